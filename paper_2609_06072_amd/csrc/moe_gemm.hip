@@ -30,6 +30,8 @@
 // Block order.  Blocks are dealt to the 8 XCDs round-robin; block b takes
 // tile (b % 8) * ceil(n_tiles / 8) + b / 8, so each XCD walks a contiguous
 // run of tiles (expert-major): an expert's weight slices stay in one L2.
+#include <type_traits>
+
 #include "ace_device.hpp"
 #include "ace_internal.hpp"
 
@@ -60,6 +62,7 @@ struct GCfg {
 using MoeSmall = GCfg<2, 2, 3>;
 using MoeBig = GCfg<4, 2, 4>;
 constexpr long kBigRows = 1024;
+constexpr int kRowGroup = 8;
 
 // Epilogue passes over column slices so that the C tile [BM][BN/NH + pad]
 // fits the stage buffers.
@@ -308,6 +311,329 @@ __global__ __launch_bounds__(C::THREADS, 512 / C::THREADS) void moe_gemm_kernel(
   }
 }
 
+// ---------------------------------------------------------------- bf16, large tiles
+//
+// 256 rows x 256 columns per block, four waves of 128 x 128 (one per SIMD).
+//
+// What bounds it: the copies' latency.  The L1 returns its lines in order, so
+// an x line that hits the L2 waits behind W lines coming from HBM; with one
+// 64 KB stage in flight per CU the copies took 1.8 us per stage of 1.0 us of
+// matrix work.  So the LDS (all 160 KB) is a ring of five 32 KB slots, each
+// freed after half a stage: a half-step works on one half of a wave's rows
+// over all 64 contraction indices of the stage (64 matrix instructions),
+// while it reads the next half's x fragments and half of the next stage's W
+// fragments into registers.  Four slots (128 KB) are then in flight, and
+// pieces stay whole cache lines (128 bytes of a row: halves split by
+// contraction index would fetch each line of the L2 twice).
+//
+// Slot P[v] holds what half-step v reads: x unit v + 1 and W unit v + 2, where
+// unit u is the half h = u & 1 (64 of each wave's 128 rows) of stage u >> 1.
+// The fragment reads and copies are placed between the matrix instructions by
+// hand (groups of four): the one wave of a SIMD has nobody to hide behind.
+struct Large {
+  static constexpr int BM = 256, BN = 256, THREADS = 256;
+  static constexpr int KC = 64, ROWB = 2 * KC;            // indices and bytes of a row per stage
+  static constexpr int UNIT = 128 * ROWB, SLOT = 2 * UNIT, SLOTS = 5;
+  static constexpr int COPIES = 8;                        // 8-row copies per wave and slot
+  static constexpr int HC = BN / 2, CST = HC + 8;         // epilogue: column halves
+};
+
+// Chunk position of a row's 16-byte chunk 0 (eight chunks per row).  Any 8
+// consecutive rows, and any 8 even or odd rows among 16, take 8 positions.
+__device__ inline int l_swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
+
+// Key of a tile when key q owns ceil(rows / BM) * per tiles, key-major: its
+// segment [lo, hi) and the tile's index among the key's tiles (wave-level,
+// every lane gets the result; false past the last tile).
+__device__ inline bool locate_key(const int32_t* offsets, int n_keys, int BM, int per, int tile,
+                                  int* q_out, int* lo_out, int* hi_out, int* rem_out) {
+  constexpr int KPL = kMaxKeys / 64;
+  const int lane = threadIdx.x & 63;
+  int off[KPL + 1], cnt = 0;
+#pragma unroll
+  for (int i = 0; i <= KPL; ++i) off[i] = offsets[min(lane * KPL + i, n_keys)];
+#pragma unroll
+  for (int i = 0; i < KPL; ++i) cnt += (off[i + 1] - off[i] + BM - 1) / BM * per;
+  int incl = cnt;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += v;
+  }
+  const int excl = incl - cnt;
+  const unsigned long long hit = __ballot(tile >= excl && tile < incl);
+  if (hit == 0ull) return false;
+  const int owner = __builtin_ctzll(hit);
+  int t = tile - excl, q = 0, lo = 0, hi = 0, rem = 0;
+  bool found = false;
+#pragma unroll
+  for (int i = 0; i < KPL; ++i) {
+    const int n = (off[i + 1] - off[i] + BM - 1) / BM * per;
+    if (!found && t < n) {
+      q = lane * KPL + i;
+      lo = off[i];
+      hi = off[i + 1];
+      rem = t;
+      found = true;
+    }
+    if (!found) t -= n;
+  }
+  *q_out = __builtin_amdgcn_readfirstlane(__shfl(q, owner, 64));
+  *lo_out = __builtin_amdgcn_readfirstlane(__shfl(lo, owner, 64));
+  *hi_out = __builtin_amdgcn_readfirstlane(__shfl(hi, owner, 64));
+  *rem_out = __builtin_amdgcn_readfirstlane(__shfl(rem, owner, 64));
+  return true;
+}
+
+// D += A B with D held in accumulation registers: with 256 of them the
+// compiler's own choice moves accumulators between register files inside the
+// loop.  The compiler's hazard tables don't see the instruction: s_nop covers
+// operands written by a vector instruction right before it, and mfma_done()
+// stands between the last one and the first read of an accumulator.
+__device__ inline void mfma_acc(f32x4& d, bf16x8 a, bf16x8 b) {
+  asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+}
+__device__ inline void mfma_done() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+// RAGGED: d_in is no multiple of two stages; the chunks past it are zeroed in
+// the fragments.
+template <bool RAGGED>
+__global__ __launch_bounds__(Large::THREADS, 1) void moe_gemm_large_kernel(MoeArgs a) {
+  using C = Large;
+  using F = bf16x8;
+  constexpr int ROWB = C::ROWB, NC = C::COPIES;
+  __shared__ __attribute__((aligned(16))) char smem[C::SLOTS * C::SLOT];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c16 = lane & 15, g = lane >> 4;
+  const int wy = wave >> 1, wx = wave & 1;
+
+  // ---- which tile: runs of tiles per XCD; within an expert, groups of up to
+  // eight row tiles walk the columns together (their x rows and each
+  // column's W rows stay in the XCD's L2)
+  const int n_tiles = count_tiles(a.offsets, a.E, C::BM) * a.nt;
+  const int per_xcd = (n_tiles + kXcds - 1) / kXcds;
+  const int bi = blockIdx.x / kXcds;
+  const int tile = (blockIdx.x % kXcds) * per_xcd + bi;
+  if (bi >= per_xcd || tile >= n_tiles) return;
+  int e, lo, hi, rem;
+  if (!locate_key(a.offsets, a.E, C::BM, a.nt, tile, &e, &lo, &hi, &rem)) return;
+  const int m_e = (hi - lo + C::BM - 1) / C::BM;
+  const int grp = rem / (kRowGroup * a.nt), gsz = min(kRowGroup, m_e - grp * kRowGroup);
+  const int ing = rem - grp * kRowGroup * a.nt;
+  const int n0 = (ing / gsz) * C::BN;
+  const int u0 = lo + (grp * kRowGroup + ing % gsz) * C::BM;
+
+  const __bf16* X = static_cast<const __bf16*>(a.x);
+  const __bf16* Wt = static_cast<const __bf16*>(a.W) + (size_t)e * a.d_out * a.d_in;
+  const int d_in = a.d_in, d_out = a.d_out;
+  const int nst = (d_in + C::KC - 1) / C::KC;
+
+  // pair of a tile row (rows past the segment repeat its last row)
+  auto pair_of = [&](int u) {
+    const int uc = min(u, hi - 1);
+    return a.row_token[uc] * a.k + (__builtin_ctz(a.row_slots[uc] | 0x80000000u) & 31);
+  };
+  // ---- copies: waves 0 and 1 copy the x rows of waves (wy = 0, 1), waves 2
+  // and 3 the W rows of (wx = 0, 1): of a slot the eight 8-row copies of their
+  // 64 rows, lane l the chunk at position l & 7 of row l >> 3.  Rows are byte
+  // offsets from x or from the tile's first W row; chunks past d_in repeat the
+  // row's last one (masked in the x fragments of the last stage).
+  const int crl = lane >> 3, cpos = lane & 7;
+  const bool xwave = wave < 2;
+  const char* base = xwave ? reinterpret_cast<const char*>(X)
+                           : reinterpret_cast<const char*>(Wt + (size_t)n0 * d_in);
+  uint32_t roff[2][NC];   // slots P[v] of even and of odd v
+#pragma unroll
+  for (int par = 0; par < 2; ++par)
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const int h = xwave ? 1 - par : par;   // x unit v + 1, W unit v + 2
+      const int row = 128 * (wave & 1) + 64 * h + 8 * i + crl;
+      int src;
+      if (xwave) {
+        const int uc = min(u0 + row, hi - 1);
+        src = a.per_pair ? pair_of(uc) : a.row_token[uc];
+      } else {
+        src = min(row, d_out - 1 - n0);
+      }
+      roff[par][i] = (uint32_t)src * (uint32_t)(2 * d_in);
+    }
+  // chunk of the copied row: the swizzle's bit 3 alternates with i
+  const int col[2] = {8 * (cpos ^ l_swz(crl)), 8 * (cpos ^ l_swz(8 + crl))};
+  const uint32_t cbase = lds_addr(smem) + (xwave ? 0 : C::UNIT) + (wave & 1) * (C::UNIT / 2);
+  uint32_t cslot = cbase;             // where this wave's copies of the next slot go
+  uint32_t colb[2];                   // byte column of a lane's chunk, by copy parity
+  auto begin_copies = [&](int v) {    // of slot P[v]
+    const int st = max(0, min((v + (xwave ? 1 : 2)) >> 1, nst - 1));
+#pragma unroll
+    for (int c = 0; c < 2; ++c) colb[c] = 2 * min(st * C::KC + col[c], d_in - 8);
+  };
+  auto copy = [&](int par, int i) {
+    const char* p = base + (size_t)(roff[par][i] + colb[i & 1]);
+    dma16(p, __builtin_amdgcn_readfirstlane(cslot + i * 1024));
+  };
+  auto end_copies = [&]() {
+    cslot += C::SLOT;
+    if (cslot >= cbase + C::SLOTS * C::SLOT) cslot = cbase;
+  };
+#pragma unroll
+  for (int v = -2; v < 2; ++v) {
+    begin_copies(v);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) copy(v & 1, i);
+    end_copies();
+  }
+
+  f32x4 acc[8][8];
+#pragma unroll
+  for (int nb = 0; nb < 8; ++nb)
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  F x0[4], x1a[4], x1b[4], wa[16], wb[16];   // x: K-block 0 and 1 of a half, W: [nb + 8 kh]
+  // ---- adapter K-blocks: acc[n][m] += sum_rho B_q[n][rho] h_m[rho], from registers
+  if (a.H) {
+    const int q = a.key_of[e];
+    const int r_q = a.keys.rank[q];
+    const __bf16* Bq = static_cast<const __bf16*>(a.B) + (size_t)d_out * a.keys.roff[q];
+    const __bf16* Hm = static_cast<const __bf16*>(a.H);
+    const bool bvec = (r_q & 7) == 0;
+    int hrow[8];
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) {
+      const int u = u0 + 128 * wy + 16 * mb + c16;
+      hrow[mb] = u < hi ? a.h_row[pair_of(u)] : -1;
+    }
+    for (int kb = 0; kb * 32 < r_q; ++kb) {
+      const int rho = kb * 32 + 8 * g;
+#pragma unroll
+      for (int nb = 0; nb < 8; ++nb) {
+        const int n = min(n0 + 128 * wx + 16 * nb + c16, d_out - 1);
+        wa[nb] = load_frag<__bf16>(Bq + (size_t)n * r_q + rho, r_q - rho, bvec);
+      }
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb)
+        wa[8 + mb] = hrow[mb] >= 0 ? Tr<__bf16>::load(Hm + (size_t)hrow[mb] * a.rpad + rho) : Tr<__bf16>::zero();
+#pragma unroll
+      for (int nb = 0; nb < 8; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) mfma_acc(acc[nb][mb], wa[nb], wa[8 + mb]);
+    }
+  }
+
+  // ---- main loop over d_in.  Fragment rows 64 wy + 16 mb + c16 of an x unit
+  // and 64 wx + 16 nb + c16 of a W unit: their swizzle depends on c16 only;
+  // K-block kh of the stage is chunk 4 kh + g, the lane's base with bit 6
+  // flipped for kh = 1.
+  const int xl = (64 * wy + c16) * ROWB + ((g ^ l_swz(c16)) << 4);
+  const int wl = C::UNIT + (64 * wx + c16) * ROWB + ((g ^ l_swz(c16)) << 4);
+  int rslot = 0;                      // slot that the half-step reads
+  // Half-step v = 2 st + h (h = PAR): matrix work on (xc, wc) for the wave's
+  // row blocks 4 h .. 4 h + 3; reads slot P[v]: the next half's x fragments
+  // into xn, the W fragments nb = 4 h .. 4 h + 3 of stage st + 1 into wn;
+  // copies slot P[v + 4] over the one that half-step v - 1 read.
+  auto half = [&](auto par_c, auto mma_c, int v, F (&x1)[4], F (&wc)[16],
+                  F (&x1n)[4], F (&wn)[16]) {
+    constexpr int PAR = decltype(par_c)::value;
+    constexpr bool MMA = decltype(mma_c)::value;
+    // this wave's reads of P[v - 1] are done and its copies of P[v] have
+    // landed (three later slots may be in flight); after the barrier that
+    // holds for every wave
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x4078);   // vmcnt(24) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    const char* xs = smem + rslot + xl;
+    const char* ws = smem + rslot + wl;
+    const char* xs1 = smem + rslot + (xl ^ 64);
+    const char* ws1 = smem + rslot + (wl ^ 64);
+    begin_copies(v + 4);
+    if (RAGGED && MMA && PAR == 0) {
+      const int c = (v >> 1) * C::KC + 8 * g;
+#pragma unroll
+      for (int nb = 0; nb < 8; ++nb) {
+        if (c >= d_in) wc[nb] = Tr<__bf16>::zero();
+        if (c + 32 >= d_in) wc[nb + 8] = Tr<__bf16>::zero();
+      }
+    }
+    if (RAGGED && MMA) {
+      const int c = (v >> 1) * C::KC + 8 * g;
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb) {
+        if (c >= d_in) x0[mb] = Tr<__bf16>::zero();
+        if (c + 32 >= d_in) x1[mb] = Tr<__bf16>::zero();
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (i < 8) {   // groups 0..7 work on K-block 0, groups 8..15 on K-block 1
+        if (i < 4) x1n[i] = *reinterpret_cast<const F*>(xs1 + i * 16 * ROWB);
+        wn[4 * PAR + (i & 3) + 8 * (i >> 2)] =
+            *reinterpret_cast<const F*>((i < 4 ? ws : ws1) + (i & 3) * 16 * ROWB);
+        copy(PAR, i);
+      }
+      if (i >= 8 && i < 12) x0[i - 8] = *reinterpret_cast<const F*>(xs + (i - 8) * 16 * ROWB);
+      if constexpr (MMA) {
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb) {
+          const int nb = i & 7, kh = i >> 3;
+          mfma_acc(acc[nb][4 * PAR + mb], wc[nb + 8 * kh], kh ? x1[mb] : x0[mb]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    end_copies();
+    rslot = rslot == (C::SLOTS - 1) * C::SLOT ? 0 : rslot + C::SLOT;
+  };
+  using P0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+  using Yes = std::true_type;
+  using No = std::false_type;
+  half(P0{}, No{}, -2, x1a, wb, x1b, wa);
+  half(P1{}, No{}, -1, x1b, wb, x1a, wa);
+  for (int st = 0; st < nst; st += 2) {   // two stages: the W fragments change registers
+    half(P0{}, Yes{}, 2 * st, x1a, wa, x1b, wb);
+    half(P1{}, Yes{}, 2 * st + 1, x1b, wa, x1a, wb);
+    half(P0{}, Yes{}, 2 * st + 2, x1a, wb, x1b, wa);
+    half(P1{}, Yes{}, 2 * st + 3, x1b, wb, x1a, wa);
+  }
+  wait_vmcnt<0>();   // copies past the last stage (repeats of it)
+  mfma_done();
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- epilogue: column halves of the tile through LDS, whole 16-byte pieces of y rows
+  __bf16* Cs = reinterpret_cast<__bf16*>(smem);
+  int* s_out = reinterpret_cast<int*>(smem + C::BM * C::CST * 2);   // y row of each tile row, -1 past the segment
+  __bf16* Y = static_cast<__bf16*>(a.y);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    __syncthreads();
+    if (h == 0) s_out[tid] = u0 + tid < hi ? pair_of(u0 + tid) : -1;
+    if (wx == h) {
+#pragma unroll
+      for (int nb = 0; nb < 8; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) {
+          const f32x4 v = acc[nb][mb];
+          const bf16x4 o = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+          *reinterpret_cast<bf16x4*>(Cs + (128 * wy + 16 * mb + c16) * C::CST + 16 * nb + 4 * g) = o;
+        }
+    }
+    __syncthreads();
+    constexpr int CPR = C::HC / 8;
+#pragma unroll 4
+    for (int it = tid; it < C::BM * CPR; it += C::THREADS) {
+      const int m = it / CPR, pc = (it % CPR) * 8;
+      const int orow = s_out[m], cc = n0 + h * C::HC + pc;
+      if (orow >= 0 && cc < d_out)
+        Tr<__bf16>::store(Y + (size_t)orow * d_out + cc, *reinterpret_cast<const F*>(Cs + m * C::CST + pc));
+    }
+  }
+}
+
 template <class C>
 hipError_t launch_moe_cfg(int dtype, MoeArgs a, long P, hipStream_t stream) {
   a.nt = (a.d_out + C::BN - 1) / C::BN;
@@ -321,7 +647,17 @@ hipError_t launch_moe_cfg(int dtype, MoeArgs a, long P, hipStream_t stream) {
 
 }  // namespace
 
+hipError_t launch_moe_large(MoeArgs a, long P, hipStream_t stream) {
+  a.nt = (a.d_out + Large::BN - 1) / Large::BN;
+  const long max_tiles = ((P + Large::BM - 1) / Large::BM + a.E) * a.nt;
+  const long grid = (max_tiles + kXcds - 1) / kXcds * kXcds;
+  if (a.d_in % (2 * Large::KC)) moe_gemm_large_kernel<true><<<(int)grid, Large::THREADS, 0, stream>>>(a);
+  else moe_gemm_large_kernel<false><<<(int)grid, Large::THREADS, 0, stream>>>(a);
+  return hipGetLastError();
+}
+
 hipError_t launch_moe_gemm(int dtype, const MoeArgs& a, long P, hipStream_t stream) {
+  if (dtype == ACE_BF16 && P >= 128 * a.E && 2L * (a.per_pair ? P : P / a.k) * a.d_in < (1L << 32)) return launch_moe_large(a, P, stream);
   if (P >= kBigRows * a.E) return launch_moe_cfg<MoeBig>(dtype, a, P, stream);
   return launch_moe_cfg<MoeSmall>(dtype, a, P, stream);
 }
