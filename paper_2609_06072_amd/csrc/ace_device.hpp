@@ -221,14 +221,20 @@ __device__ inline void build_bucket_table(const int32_t* offsets, const int32_t*
 // wave computes it on its own: lane l owns keys KPL*l .. KPL*l + KPL - 1, a
 // wave-level scan of the per-lane tile counts finds the owning lane, which
 // broadcasts the result (no LDS, no barrier).  Returns false (in every lane)
-// when the tile is past the last one.
+// when the tile is past the last one.  With seg_map, the segments are
+// seg_map[offsets[q]] .. seg_map[offsets[q+1]]; lo_out: the segment's start.
 __device__ inline bool locate_tile(const int32_t* offsets, int n_keys, int BM, int tile, int* q_out,
-                                   int* u0_out, int* uend_out) {
+                                   int* u0_out, int* uend_out, const int32_t* seg_map = nullptr,
+                                   int* lo_out = nullptr) {
   constexpr int KPL = kMaxKeys / 64;
   const int lane = threadIdx.x & 63;
   int off[KPL + 1], tl[KPL];
 #pragma unroll
   for (int i = 0; i <= KPL; ++i) off[i] = offsets[min(lane * KPL + i, n_keys)];
+  if (seg_map) {
+#pragma unroll
+    for (int i = 0; i <= KPL; ++i) off[i] = seg_map[off[i]];
+  }
   int cnt = 0;
 #pragma unroll
   for (int i = 0; i < KPL; ++i) {
@@ -245,7 +251,7 @@ __device__ inline bool locate_tile(const int32_t* offsets, int n_keys, int BM, i
   const unsigned long long hit = __ballot(tile >= excl && tile < incl);
   if (hit == 0ull) return false;
   const int owner = __builtin_ctzll(hit);
-  int t = tile - excl, q = 0, u0 = 0, ue = 0;
+  int t = tile - excl, q = 0, u0 = 0, ue = 0, lo = 0;
   bool found = false;
 #pragma unroll
   for (int i = 0; i < KPL; ++i) {
@@ -253,6 +259,7 @@ __device__ inline bool locate_tile(const int32_t* offsets, int n_keys, int BM, i
       q = lane * KPL + i;
       u0 = off[i] + t * BM;
       ue = off[i + 1];
+      lo = off[i];
       found = true;
     }
     if (!found) t -= tl[i];
@@ -260,6 +267,7 @@ __device__ inline bool locate_tile(const int32_t* offsets, int n_keys, int BM, i
   *q_out = __shfl(q, owner, 64);
   *u0_out = __shfl(u0, owner, 64);
   *uend_out = __shfl(ue, owner, 64);
+  if (lo_out) *lo_out = __shfl(lo, owner, 64);
   return true;
 }
 

@@ -277,13 +277,18 @@ __global__ __launch_bounds__(kThreads) void contract_kernel(ContractArgs a) {
 // a window of 65 - k positions, so their pairs (at most 64) are all in the
 // tile; the per-pair results times the pair weights go to LDS in fp32 and
 // every row's sum (pairs in position order) is stored once.
-template <int RB, int NWV>
+//
+// DEEP: with no more tiles than CUs (decode batches) a block is alone on its
+// CU and every stage would cost a round trip to memory: the stages fill the
+// LDS instead of sharing it with other blocks, a block takes one tile, found
+// without barriers.  OLMoE-like, 32 tokens: DEEPUS
+template <int RB, int NWV, bool DEEP>
 struct CDma {
   // contraction indices per stage and stages in LDS: ranks up to 32 take
   // 128-column stages two deep (three blocks per CU); larger ranks, whose
   // weight rows double the bytes of a stage, 64-column stages three deep
-  static constexpr int KC = RB <= 2 ? 128 : 64;
-  static constexpr int NBUF = RB <= 2 ? 2 : 3;  // at most 4 (see the waits)
+  static constexpr int KC = RB <= 2 || (DEEP && RB == 4) ? 128 : 64;
+  static constexpr int NBUF = DEEP ? (RB == 4 ? 4 : 6) : RB <= 2 ? 2 : 3;
   static constexpr int THREADS = 64 * NWV;       // NWV waves of 16 tile rows each
   static constexpr int ROWS = 16 * NWV;          // tile rows
   static constexpr int CPR = KC / 8;             // 16-byte chunks per row piece
@@ -300,6 +305,7 @@ struct CDma {
   static constexpr int RPS = 16 * RB + 4;   // 16-byte skew between positions
   static_assert(ROWS * RPS * 4 <= LDS, "per-pair results exceed the stage buffers");
   static_assert(WROWS / RPI <= NWV * NW, "weight copies");
+  static_assert((NBUF - 2) * (NS + NW) < 64, "copies in flight per wave");
 };
 
 // Chunk swizzle of weight row w (CPR 16-byte chunks per staged row).  A
@@ -324,11 +330,11 @@ inline __host__ __device__ int contract_tile(int row_sum, int k, int rows) {
 // 4) + l over its pairs in position order for the rank chunks 8 (w % 4),
 // 8 (w % 4) + 32, ... and stores the bf16 sum per key (column u - rfirst)
 // and/or per token.
-template <int RB, int NWV>
+template <int RB, int NWV, bool DEEP>
 __device__ inline void row_sum_store(const ContractArgs& a, int q, const f32x4 (&acc)[RB], float s,
                                      float pw, int ua, int ub, int p0, int rfirst, int rstart,
                                      int rend, int rtok, float* hp) {
-  constexpr int RPS = CDma<RB, NWV>::RPS;
+  constexpr int RPS = CDma<RB, NWV, DEEP>::RPS;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c16 = lane & 15, g = lane >> 4;
   const int r_q = a.keys.rank[q], roff = a.keys.roff[q], R = a.keys.R;
@@ -379,9 +385,9 @@ __device__ inline void row_sum_store(const ContractArgs& a, int q, const f32x4 (
   }
 }
 
-template <int RB, int NWV>
-__global__ __launch_bounds__(64 * NWV, RB == 8 ? 2 : 1) void contract_dma_kernel(ContractArgs a) {
-  using G = CDma<RB, NWV>;
+template <int RB, int NWV, bool DEEP>
+__global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_dma_kernel(ContractArgs a) {
+  using G = CDma<RB, NWV, DEEP>;
   constexpr int KC = G::KC, NBUF = G::NBUF, KB = Tr<__bf16>::KB;
   constexpr int CPR = G::CPR, RPI = G::RPI;
   // stage buffers: NBUF source stages, then NBUF weight stages; the row sums
@@ -389,20 +395,24 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 ? 2 : 1) void contract_dma_kernel
   __shared__ __attribute__((aligned(16))) char smem[G::LDS];
   char (*Sb)[G::SBYTES] = reinterpret_cast<char (*)[G::SBYTES]>(smem);
   char (*Wb)[G::WBYTES] = reinterpret_cast<char (*)[G::WBYTES]>(smem + NBUF * G::SBYTES);
-  __shared__ int seg[kMaxKeys + 1];
-  __shared__ int bstart[kMaxKeys + 1];
-  __shared__ int bfirst[kMaxKeys];
-  __shared__ int scan[kThreads];   // block_exclusive_scan reads the first kThreads / 64
+  constexpr int TAB = DEEP ? 1 : kMaxKeys + 1;   // tile tables
+  __shared__ int seg[TAB];
+  __shared__ int bstart[TAB];
+  __shared__ int bfirst[TAB];
+  __shared__ int scan[DEEP ? 1 : kThreads];   // block_exclusive_scan reads the first kThreads / 64
   static_assert(G::THREADS >= kMaxKeys, "one thread per key in the tile tables");
   const int n_keys = a.keys.n_keys;
   const int bucket = blockIdx.x % kXcds;
   const int K = a.K, k = a.k;
   const bool rsum = a.row_sum != 0;   // implies kSrcPairList
   const int TS = contract_tile(a.row_sum, k, G::ROWS);
-  build_bucket_table(a.offsets, a.src_mode == kSrcPairList ? a.ppos : nullptr, n_keys, TS, bucket,
-                     seg, bstart, bfirst, scan);
-  const int total = bstart[n_keys];
-  const int stride = gridDim.x / kXcds;  // the grid is a multiple of kXcds
+  const int32_t* seg_map = a.src_mode == kSrcPairList ? a.ppos : nullptr;
+  int total = 1, stride = 1;
+  if constexpr (!DEEP) {
+    build_bucket_table(a.offsets, seg_map, n_keys, TS, bucket, seg, bstart, bfirst, scan);
+    total = bstart[n_keys];
+    stride = gridDim.x / kXcds;  // the grid is a multiple of kXcds
+  }
   // wave-uniform values kept in scalar registers (uniform branches, no exec masks)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, g = lane >> 4;
@@ -410,12 +420,18 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 ? 2 : 1) void contract_dma_kernel
   const __bf16* W = static_cast<const __bf16*>(a.W);
   const int cpos = lane & (CPR - 1), crow = lane / CPR;   // 16-byte position / row inside a copy
 
-  for (int idx = blockIdx.x / kXcds; idx < total; idx += stride) {
-    const int q = upper_index(bstart, n_keys, idx);
-    const int lo = seg[q];
-    int u0 = lo + (bfirst[q] + idx - bstart[q]) * TS;
+  for (int idx = DEEP ? 0 : blockIdx.x / kXcds; idx < total; idx += stride) {
     const int nst = (K + KC - 1) / KC;
-    int u_end = seg[q + 1];
+    int q, lo, u0, u_end;
+    if constexpr (DEEP) {
+      if (!locate_tile(a.offsets, n_keys, TS, blockIdx.x, &q, &u0, &u_end, seg_map, &lo)) return;
+      q = __builtin_amdgcn_readfirstlane(q);
+    } else {
+      q = upper_index(bstart, n_keys, idx);
+      lo = seg[q];
+      u0 = lo + (bfirst[q] + idx - bstart[q]) * TS;
+      u_end = seg[q + 1];
+    }
     const int r_q = a.keys.rank[q], roff = a.keys.roff[q];
     // row sums: rows ua .. ub - 1 start inside the window [u0, u0 + TS); their
     // pairs are positions ppos[ua] .. ppos[ub] - 1, which become u0 .. u_end
@@ -450,6 +466,9 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 ? 2 : 1) void contract_dma_kernel
     // weight copies this wave issues per stage (rows below r_q only)
     const int wcopies = (r_q + RPI - 1) / RPI;
     const int nw = min(G::NW, max(0, wcopies - wave * G::NW));
+    // source copies: none for rows past the segment (their results are not stored)
+    const int ns = __builtin_amdgcn_readfirstlane(
+        min(G::NS, max(0, (u_end - u0 - 16 * wave + RPI - 1) / RPI)));
 
     // source rows this lane copies (rows past the segment re-read the last
     // one) and the chunk of the row piece it copies
@@ -482,15 +501,16 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 ? 2 : 1) void contract_dma_kernel
       const int k0 = st * KC;
 #pragma unroll
       for (int i = 0; i < G::NS; ++i)
-        dma16(sptr[i] + min(k0 + scol[i], K - 8),
-              __builtin_amdgcn_readfirstlane(lds_addr(&Sb[b][(16 * wave + RPI * i) * KC * 2])));
+        if (i < ns)
+          dma16(sptr[i] + min(k0 + scol[i], K - 8),
+                __builtin_amdgcn_readfirstlane(lds_addr(&Sb[b][(16 * wave + RPI * i) * KC * 2])));
 #pragma unroll
       for (int i = 0; i < G::NW; ++i)
         if (i < nw)
           dma16(wptr[i] + min(k0 + wcol[i], K - 8),
                 __builtin_amdgcn_readfirstlane(lds_addr(&Wb[b][RPI * (wave * G::NW + i) * KC * 2])));
     };
-    const int per_stage = G::NS + nw;   // copies per stage of this wave
+    const int per_stage = ns + nw;   // copies per stage of this wave
 
     __syncthreads();  // the previous tile is done with the buffers
     f32x4 acc[RB];
@@ -548,7 +568,7 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 ? 2 : 1) void contract_dma_kernel
 
     const float s = a.alpha / (float)r_q;
     if (rsum) {
-      row_sum_store<RB, NWV>(a, q, acc, s, pw, ua, ub, u0, rfirst, rstart, rend, rtok,
+      row_sum_store<RB, NWV, DEEP>(a, q, acc, s, pw, ua, ub, u0, rfirst, rstart, rend, rtok,
                              reinterpret_cast<float*>(smem));
       continue;
     }
@@ -568,13 +588,21 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 ? 2 : 1) void contract_dma_kernel
 
 template <int RB, int NWV>
 hipError_t launch_contract_dma(const ContractArgs& a, long P, hipStream_t stream) {
-  using G = CDma<RB, NWV>;
+  using G = CDma<RB, NWV, false>;
   const int TS = contract_tile(a.row_sum, a.k, G::ROWS);
+  const long tiles = P > 0 ? (P + TS - 1) / TS + a.keys.n_keys : 0;   // at most
+  if constexpr (RB <= 8) {
+    // one block per CU and one tile per block: see DEEP
+    if (tiles > 0 && tiles <= device_cu_count()) {
+      contract_dma_kernel<RB, NWV, true><<<(int)tiles, G::THREADS, 0, stream>>>(a);
+      return hipGetLastError();
+    }
+  }
   // tiles per bucket <= (all tiles) / kXcds + n_keys
-  const long pb = P > 0 ? ((P + TS - 1) / TS + a.keys.n_keys) / kXcds + a.keys.n_keys : 0;
+  const long pb = P > 0 ? tiles / kXcds + a.keys.n_keys : 0;
   const long cap = (long)G::BLOCKS_PER_CU * device_cu_count() / kXcds;
   const int grid = (int)(pb < cap ? pb : cap) * kXcds;
-  if (grid > 0) contract_dma_kernel<RB, NWV><<<grid, G::THREADS, 0, stream>>>(a);
+  if (grid > 0) contract_dma_kernel<RB, NWV, false><<<grid, G::THREADS, 0, stream>>>(a);
   return hipGetLastError();
 }
 

@@ -16,6 +16,9 @@
 //   scatter -- rebuilds the bitmap; a row's rank inside its (key, block) cell
 //              is the popcount of the lower bits, so rows come out sorted by
 //              (key, token, slot) with no atomics on rows and no sort.
+// With at most kRecountBlocks chunks (decode batches) the scatter is the only
+// launch: every block marks all chunks, its own last, and counts from the
+// bitmaps what the count launch would have written.
 // Pair positions (the routed pairs in (key, token, slot) order) follow the
 // same scheme: in ACE_ROWS_GROUP_DEDUP mode a second bitmap marks every pair
 // of a key and second cell table is scanned; in the other modes a row is a
@@ -40,6 +43,10 @@ constexpr int kWordsPerKey = kPairsPerBlock / 64;
 // the scatter folds itself: 32 KiB of LDS as 16-bit counts.
 constexpr int kFoldCells = 16384;
 
+// Chunks up to which each scatter block recounts all of them: a chunk costs a
+// block about 1.2 us, the launch that it saves about 5 us.
+constexpr int kRecountBlocks = 4;
+
 struct PermPass {
   int32_t mode, n_keys;
   int32_t fold;        // the scatter derives the cell bases itself (no scan launch)
@@ -61,6 +68,7 @@ struct PermArgs {
   const int32_t* e2g;  // null unless a pass is group-keyed
   int32_t T, k, E, G;
   int32_t tokens_per_block, nblk, npass;
+  int32_t recount;     // the scatter counts all chunks itself (no count or scan launch)
   int32_t nwords;      // 64-bit words of bitmaps (the largest pass's)
   PermPass pass[kMaxPermPasses];
 };
@@ -112,10 +120,14 @@ __device__ inline int mark_pass(const PermArgs& a, const PermPass& P, int np, co
     const int e = eid[t];
     q = e < 0 ? -1 : (P.mode == ACE_ROWS_EXPERT ? e : gmap[e]);
     // the routed experts of a token form a set: an id already listed at a
-    // lower slot of the same token drops this pair
+    // lower slot of the same token drops this pair (four reads in flight)
     const int j = t % a.k, tb = t - j;
-    for (int jj = 0; jj < j; ++jj)
-      if (eid[tb + jj] == e) q = -1;
+    for (int jj = 0; jj < j; jj += 4) {
+      int o[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = eid[tb + min(jj + i, j - 1)];
+      if (o[0] == e || o[1] == e || o[2] == e || o[3] == e) q = -1;
+    }
     keys[t] = q;
   }
   __syncthreads();
@@ -129,11 +141,15 @@ __device__ inline int mark_pass(const PermArgs& a, const PermPass& P, int np, co
       if (dedup) {
         // leader = first slot of the token with this group; mask = all of them
         const int j = t % k, tb = t - j;
-        for (int jj = 0; jj < k; ++jj) {
-          if (keys[tb + jj] != q) continue;
-          if (jj < j) { emit = false; break; }
-          m |= 1u << jj;
+        for (int jj = 0; jj < k; jj += 4) {
+          int o[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[i] = keys[tb + min(jj + i, k - 1)];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (jj + i < k && o[i] == q) m |= 1u << (jj + i);
         }
+        emit = (m & ((1u << j) - 1u)) == 0u;
       }
       masks[t] = emit ? m : 0u;
       if (emit) atomicOr(&bits[q * kWordsPerKey + (t >> 6)], 1ull << (t & 63));
@@ -380,6 +396,63 @@ __device__ void fold_pass(const PermArgs& a, const PermPass& P, int b, uint16_t*
   __syncthreads();
 }
 
+// The same from the ids themselves (a.recount): marks every chunk of pass P,
+// block b's last, so that its ids, keys, masks and bitmaps are left in LDS.
+__device__ void recount_pass(const PermArgs& a, const PermPass& P, int b, int* eid, int* gmap,
+                             int* keys, uint32_t* masks, unsigned long long* bits, int* cbase,
+                             int* pbase, int* red) {
+  const int t = threadIdx.x;
+  const bool dedup = P.mode == ACE_ROWS_GROUP_DEDUP;
+  const int chunk = a.tokens_per_block * a.k, n_keys = P.n_keys;
+  auto pairs = [&](int c) { return min(chunk, a.T * a.k - c * chunk); };
+  Staged ids[kRecountBlocks];   // chunk order: the others, then b
+#pragma unroll
+  for (int i = 0; i < kRecountBlocks; ++i) {
+    const int c = i == a.nblk - 1 ? b : i < b ? i : i + 1;
+    if (i < a.nblk) ids[i] = issue_ids(a, c * chunk, pairs(c));
+  }
+  int st = 0, sp = 0, pt = 0, pp = 0, d = 0;
+#pragma unroll
+  for (int i = 0; i < kRecountBlocks; ++i) {
+    if (i >= a.nblk) continue;   // block-uniform
+    const int c = i == a.nblk - 1 ? b : i < b ? i : i + 1;
+    store_ids(a, ids[i], eid, gmap, bits);
+    d += mark_pass(a, P, pairs(c), eid, gmap, keys, masks, bits);
+    int n = 0, pn = 0;
+    if (t < n_keys) {
+#pragma unroll
+      for (int w = 0; w < kWordsPerKey; ++w) {
+        n += __popcll(bits[t * kWordsPerKey + w]);
+        if (dedup) pn += __popcll(bits[(n_keys + t) * kWordsPerKey + w]);
+      }
+    }
+    st += n;
+    pt += pn;
+    if (c < b) {
+      sp += n;
+      pp += pn;
+    }
+    if (i < a.nblk - 1) __syncthreads();   // the bitmaps are cleared next
+  }
+  int U, npairs, dt;
+  const int ks = block_exclusive_scan(st, red, &U);
+  const int pks = block_exclusive_scan(pt, red, &npairs);
+  if (t < n_keys) {
+    cbase[t] = ks + sp;
+    pbase[t] = pks + pp;
+    if (b == 0) {
+      P.offsets[t] = ks;
+      P.counts[t] = st;
+    }
+  }
+  block_exclusive_scan(d, red, &dt);
+  if (b == 0 && t == 0) {
+    P.offsets[n_keys] = U;
+    P.row_pair[U] = dedup ? npairs : U;
+    *P.n_dropped = dt;
+  }
+}
+
 __global__ __launch_bounds__(kThreads) void permute_scatter_kernel(PermArgs a) {
   extern __shared__ unsigned long long bits[];   // the pass's bitmaps, then its count tables
   __shared__ int eid[kPairsPerBlock];
@@ -394,13 +467,17 @@ __global__ __launch_bounds__(kThreads) void permute_scatter_kernel(PermArgs a) {
   const int k = a.k;
   const int p0 = b * a.tokens_per_block * k;
   const int np = min(a.tokens_per_block * k, a.T * k - p0);
-  // the ids are in flight while the cell tables are staged
-  const Staged ids = issue_ids(a, p0, np);
-  if (P.fold)
-    fold_pass(a, P, b, reinterpret_cast<uint16_t*>(bits + a.nwords), tot, pre, ptot, ppre, cbase,
-              pbase, red);
-  store_ids(a, ids, eid, gmap, bits);
-  mark_pass(a, P, np, eid, gmap, keys, masks, bits);
+  if (a.recount) {
+    recount_pass(a, P, b, eid, gmap, keys, masks, bits, cbase, pbase, red);
+  } else {
+    // the ids are in flight while the cell tables are staged
+    const Staged ids = issue_ids(a, p0, np);
+    if (P.fold)
+      fold_pass(a, P, b, reinterpret_cast<uint16_t*>(bits + a.nwords), tot, pre, ptot, ppre, cbase,
+                pbase, red);
+    store_ids(a, ids, eid, gmap, bits);
+    mark_pass(a, P, np, eid, gmap, keys, masks, bits);
+  }
   const int lp = threadIdx.x;
   if (lp >= np) return;
   const int q = keys[lp];
@@ -414,7 +491,8 @@ __global__ __launch_bounds__(kThreads) void permute_scatter_kernel(PermArgs a) {
   const int w = lp >> 6;
   int rank = __popcll(kb[w] & ((1ull << (lp & 63)) - 1ull));
   for (int i = 0; i < w; ++i) rank += __popcll(kb[i]);
-  const int row = (P.fold ? cbase[q] : P.cell[q * a.nblk + b]) + rank;
+  const bool based = a.recount || P.fold;
+  const int row = (based ? cbase[q] : P.cell[q * a.nblk + b]) + rank;
   const int tok = (p0 + lp) / k;
   P.row_token[row] = tok;
   P.row_slots[row] = m;
@@ -423,7 +501,7 @@ __global__ __launch_bounds__(kThreads) void permute_scatter_kernel(PermArgs a) {
     const unsigned long long* pb = bits + (P.n_keys + q) * kWordsPerKey;
     int prank = __popcll(pb[w] & ((1ull << (lp & 63)) - 1ull));
     for (int i = 0; i < w; ++i) prank += __popcll(pb[i]);
-    pos = (P.fold ? pbase[q] : P.pcell[q * a.nblk + b]) + prank;
+    pos = (based ? pbase[q] : P.pcell[q * a.nblk + b]) + prank;
   }
   P.row_pair[row] = pos;
   for (uint32_t mm = m; mm; mm &= mm - 1u) {
@@ -456,6 +534,7 @@ hipError_t launch_permute(const int32_t* ids, int T, int k, int E, const int32_t
   a.tokens_per_block = permute_tokens_per_block(k);
   a.nblk = T > 0 ? (T + a.tokens_per_block - 1) / a.tokens_per_block : 0;
   a.npass = npass;
+  a.recount = a.nblk > 0 && a.nblk <= kRecountBlocks;
   bool scan = false;
   int words = 0;          // the largest pass's bitmaps
   size_t tab_bytes = 0;   // the largest staged count tables of a folding pass
@@ -476,9 +555,9 @@ hipError_t launch_permute(const int32_t* ids, int T, int k, int E, const int32_t
     P.n_dropped = o.rt->n_dropped;
     P.row_pair = o.rt->row_pair;
     P.pair_list = o.rt->pair_list;
-    P.fold = a.nblk > 0 &&
+    P.fold = a.nblk > 0 && !a.recount &&
              (long)a.nblk * o.n_keys * (o.mode == ACE_ROWS_GROUP_DEDUP ? 2 : 1) <= kFoldCells;
-    scan = scan || !P.fold;
+    scan = scan || !(P.fold || a.recount);
     if (P.fold) {
       const size_t tb = (size_t)a.nblk * o.n_keys * sizeof(uint16_t) *
                         (o.mode == ACE_ROWS_GROUP_DEDUP ? 2 : 1);
@@ -487,7 +566,7 @@ hipError_t launch_permute(const int32_t* ids, int T, int k, int E, const int32_t
   }
   a.nwords = words;
   const size_t lds = (size_t)words * sizeof(unsigned long long);
-  if (a.nblk > 0) permute_count_kernel<<<a.nblk * npass, kThreads, lds, stream>>>(a);
+  if (a.nblk > 0 && !a.recount) permute_count_kernel<<<a.nblk * npass, kThreads, lds, stream>>>(a);
   if (scan) permute_scan_kernel<<<npass, 1024, 0, stream>>>(a);
   if (a.nblk > 0) permute_scatter_kernel<<<a.nblk * npass, kThreads, lds + tab_bytes, stream>>>(a);
   return hipGetLastError();
