@@ -309,19 +309,24 @@ __device__ inline void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// s_waitcnt vmcnt(n) for a wave-uniform 0 <= n <= N
-template <int N>
-__device__ inline void wait_vmcnt_upto(int n) {
-  if constexpr (N > 0) {
-    if (n >= N) {
-      wait_vmcnt<N>();
-      return;
-    }
-    wait_vmcnt_upto<N - 1>(n);
+// s_waitcnt vmcnt(n) for a wave-uniform LO <= n <= N (the counter is part of
+// the instruction: a binary search over them, the largest first as it is the
+// steady state of the loops)
+template <int LO, int N>
+__device__ inline void wait_vmcnt_in(int n) {
+  if constexpr (LO < N) {
+    constexpr int MID = (LO + N + 1) / 2;
+    if (n >= MID) wait_vmcnt_in<MID, N>(n);
+    else wait_vmcnt_in<LO, MID - 1>(n);
   } else {
     (void)n;
-    wait_vmcnt<0>();
+    wait_vmcnt<N>();
   }
+}
+template <int N>
+__device__ inline void wait_vmcnt_upto(int n) {
+  if (n >= N) wait_vmcnt<N>();
+  else if constexpr (N > 0) wait_vmcnt_in<0, N - 1>(n);
 }
 
 }  // namespace ace

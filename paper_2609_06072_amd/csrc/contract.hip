@@ -262,6 +262,118 @@ __global__ __launch_bounds__(kThreads) void contract_kernel(ContractArgs a) {
   }
 }
 
+// ------------------------------------------------------------- small batches
+//
+// Few rows (decode batches): latency bounds a tile, not bytes.  A block of 16
+// waves takes a tile of 16 rows; the waves split the contraction (wave w takes
+// K-blocks w, w + 16, ...), and each loads its fragments straight from global
+// memory, up to SU K-blocks in flight, so that a contraction of 2048 is one or
+// two round trips; the partial sums meet in LDS in wave order.  OLMoE-like,
+// 32 tokens, d_in 2048: 12.9 -> 9.4 us a call; fp32, 256 tokens,
+// d_in 512 and 1024: 11.5 -> 8.8 and 15.2 -> 7.8 us.
+// tiles (at most) up to which small batches go this way: above, the tiles
+// re-read the weights too often (1000 tokens, 564 tiles: a pass of the three
+// adapters takes 105 us with it, 86 without; 400 tokens, 216 tiles: 67 against 71)
+constexpr long kSmallTiles = 256;
+template <int RB>
+struct CSmall {
+  static constexpr int NWV = 16;
+  static constexpr int SU = RB <= 4 ? 4 : RB == 8 ? 2 : 1;   // K-blocks in flight per wave
+  static constexpr int RRB = RB < 8 ? RB : 8;                // rank blocks per reduction pass
+};
+
+template <typename T, int RB>
+__global__ __launch_bounds__(64 * CSmall<RB>::NWV) void contract_small_kernel(ContractArgs a) {
+  using F = typename Tr<T>::frag;
+  using G = CSmall<RB>;
+  constexpr int PER = Tr<T>::PER, KB = Tr<T>::KB, SU = G::SU, NWV = G::NWV;
+  __shared__ f32x4 red[NWV][G::RRB][64];
+  const int n_keys = a.keys.n_keys;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15, g = lane >> 4;
+  int q, u0, u_end, lo;
+  if (!locate_tile(a.offsets, n_keys, 16, blockIdx.x, &q, &u0, &u_end,
+                   a.src_mode == kSrcPairList ? a.ppos : nullptr, &lo))
+    return;
+  q = __builtin_amdgcn_readfirstlane(q);
+  const int r_q = a.keys.rank[q], roff = a.keys.roff[q];
+  const int nrb = (r_q + KB - 1) / KB * Tr<T>::APF;
+  const int K = a.K, k = a.k;
+  // rows past the segment repeat its last row and weight rows past r_q the
+  // last one (never stored, zeroed before any store): every load is unconditional
+  const int u = u0 + c16, uc = min(u, u_end - 1);
+  int sr;
+  if (a.src_mode == kSrcPairList) {
+    sr = a.plist[uc];
+  } else {
+    const int tok = a.row_token[uc];
+    const uint32_t sl = a.row_slots[uc];
+    sr = a.src_mode == kSrcPerPair ? tok * k + (__builtin_ctz(sl | 0x80000000u) & 31) : tok;
+  }
+  const T* srow = static_cast<const T*>(a.src) + (size_t)sr * K;
+  const T* wrow[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int r = rank_of_row<T>(rb, c16);
+    wrow[rb] = static_cast<const T*>(a.W) + (size_t)(roff + min(r, r_q - 1)) * a.ldw;
+  }
+  f32x4 acc[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nks = (K + KB - 1) / KB;
+  for (int ks = wave; ks < nks; ks += NWV * SU) {
+    F sf[SU], wf[SU][RB];
+    // K-blocks past the end repeat the last chunk of the row, with x zeroed
+#pragma unroll
+    for (int s = 0; s < SU; ++s) {
+      const int kof = (ks + NWV * s) * KB + PER * g, kc = min(kof, K - PER);
+      sf[s] = Tr<T>::load(srow + kc);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+        if (rb < nrb) wf[s][rb] = Tr<T>::load(wrow[rb] + kc);
+    }
+#pragma unroll
+    for (int s = 0; s < SU; ++s) {
+      const int kof = (ks + NWV * s) * KB + PER * g;
+      if (kof >= K) sf[s] = Tr<T>::zero();
+      if (ks + NWV * s < nks) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+          if (rb < nrb) acc[rb] = Tr<T>::mma(wf[s][rb], sf[s], acc[rb]);
+      }
+    }
+  }
+  // partial sums: wave 0 adds them in wave order and finishes the tile
+  const float s = a.alpha / (float)r_q;
+  f32x4 h[RB];
+#pragma unroll
+  for (int p = 0; p < RB / G::RRB; ++p) {
+    if (p > 0) __syncthreads();
+#pragma unroll
+    for (int rb = 0; rb < G::RRB; ++rb) red[wave][rb][lane] = acc[p * G::RRB + rb];
+    __syncthreads();
+    // wave w sums rank block w's partials
+    if (wave < G::RRB) {
+      f32x4 t = red[0][wave][lane];
+#pragma unroll
+      for (int w = 1; w < NWV; ++w) t += red[w][wave][lane];
+      red[0][wave][lane] = t;
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int rb = 0; rb < G::RRB; ++rb) h[p * G::RRB + rb] = red[0][rb][lane] * s;
+    }
+  }
+  if (wave != 0 || u >= u_end) return;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (rank_of_row<T>(rb, 4 * g + v) >= r_q) h[rb][v] = 0.f;
+  contract_store<T, RB>(a, q, lo, u, h);
+}
+
 // ------------------------------------------------------------- bf16 path
 //
 // A block takes a tile of 64 rows of one key; wave w owns rows 16w .. 16w+15
@@ -281,7 +393,8 @@ __global__ __launch_bounds__(kThreads) void contract_kernel(ContractArgs a) {
 // DEEP: with no more tiles than CUs (decode batches) a block is alone on its
 // CU and every stage would cost a round trip to memory: the stages fill the
 // LDS instead of sharing it with other blocks, a block takes one tile, found
-// without barriers.  OLMoE-like, 32 tokens: DEEPUS
+// without barriers.  OLMoE-like, 1000 tokens (188 tiles at most): a pass of
+// the three adapters 96 -> 86 us.
 template <int RB, int NWV, bool DEEP>
 struct CDma {
   // contraction indices per stage and stages in LDS: ranks up to 32 take
@@ -608,6 +721,11 @@ hipError_t launch_contract_dma(const ContractArgs& a, long P, hipStream_t stream
 
 template <typename T, int RB>
 hipError_t launch_contract_rb(const ContractArgs& a, long P, hipStream_t stream) {
+  const long small_tiles = P > 0 ? (P + 15) / 16 + a.keys.n_keys : 0;   // at most
+  if (small_tiles > 0 && small_tiles <= kSmallTiles && !a.row_sum) {
+    contract_small_kernel<T, RB><<<(int)small_tiles, 64 * CSmall<RB>::NWV, 0, stream>>>(a);
+    return hipGetLastError();
+  }
   constexpr int BM = 16 * CGeo<RB>::NRB;
   // tiles per bucket <= (all tiles) / kXcds + n_keys
   const long per_bucket = P > 0 ? ((P + BM - 1) / BM + a.keys.n_keys) / kXcds + a.keys.n_keys : 0;
