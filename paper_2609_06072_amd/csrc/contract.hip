@@ -10,10 +10,8 @@
 // With out_w, the result of a single-pair row is multiplied by the pair's
 // weight.
 //
-// A block takes a tile of BM rows of one key.  The four waves split the
-// contraction (wave w takes K-blocks w, w+4, ...), so each source row and each
-// weight row is read once per tile, and the partial sums meet in LDS in a
-// fixed order (deterministic).  Results go to any of three layouts:
+// Every sum is formed in a fixed order (deterministic).  Results go to any of
+// three layouts:
 //   row-major  [U][rpad]      operand of the expand kernel (zero beyond r_q)
 //   per key    [R][ldh]       column u - offsets[q]: operand of the column pass
 //   dense      [T*kslots][R]  per-token rows: operand of the dense dx GEMM
@@ -101,167 +99,6 @@ __device__ inline void contract_store(const ContractArgs& a, int q, int lo, int 
   }
 }
 
-template <int RB>
-struct CGeo {
-  static constexpr int NRB = RB <= 4 ? 4 : (RB == 8 ? 2 : 1);
-  static constexpr int UNROLL = RB <= 8 ? 2 : 1;
-};
-
-template <typename T, int RB>
-__global__ __launch_bounds__(kThreads) void contract_kernel(ContractArgs a) {
-  using F = typename Tr<T>::frag;
-  constexpr int PER = Tr<T>::PER, KB = Tr<T>::KB, APF = Tr<T>::APF;
-  constexpr int NRB = CGeo<RB>::NRB, U = CGeo<RB>::UNROLL;
-  constexpr int BM = 16 * NRB;
-  __shared__ int seg[kMaxKeys + 1];
-  __shared__ int bstart[kMaxKeys + 1];
-  __shared__ int bfirst[kMaxKeys];
-  __shared__ int scan[kThreads];
-  __shared__ f32x4 red[4][NRB][RB][64];
-  const int n_keys = a.keys.n_keys;
-  const int bucket = blockIdx.x % kXcds;
-  build_bucket_table(a.offsets, a.src_mode == kSrcPairList ? a.ppos : nullptr, n_keys, BM, bucket,
-                     seg, bstart, bfirst, scan);
-  const int total = bstart[n_keys];
-  const int stride = gridDim.x / kXcds;  // the grid is a multiple of kXcds
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int c16 = lane & 15, g = lane >> 4;
-  const T* S = static_cast<const T*>(a.src);
-  const T* W = static_cast<const T*>(a.W);
-  const int K = a.K, k = a.k;
-  const int nks = (K + KB - 1) / KB, nks_full = K / KB;
-
-  for (int idx = blockIdx.x / kXcds; idx < total; idx += stride) {
-    const int q = upper_index(bstart, n_keys, idx);
-    const int lo = seg[q];
-    const int u0 = lo + (bfirst[q] + idx - bstart[q]) * BM;
-    const int u_end = seg[q + 1];
-    const int r_q = a.keys.rank[q], roff = a.keys.roff[q];
-    const int nmb = (r_q + KB - 1) / KB;
-    const int nrb = nmb * APF;  // rank blocks spanned by rank_of_row for r < r_q
-
-    // Source rows.  Rows past the segment re-read the last row (never
-    // stored); weight rows past r_q re-read row r_q - 1 (zeroed before any
-    // store), so every load is unconditional and a wave keeps all of them in
-    // flight.
-    const T* srow[NRB];
-    int sv[NRB];
-    uint32_t slv[NRB];
-#pragma unroll
-    for (int ib = 0; ib < NRB; ++ib) {  // unconditional loads: one round trip
-      const int uc = min(u0 + 16 * ib + c16, u_end - 1);
-      if (a.src_mode == kSrcPairList) {
-        sv[ib] = a.plist[uc];
-        slv[ib] = 1u;
-      } else {
-        sv[ib] = a.row_token[uc];
-        slv[ib] = a.row_slots[uc];
-      }
-    }
-#pragma unroll
-    for (int ib = 0; ib < NRB; ++ib) {
-      const int j0 = __builtin_ctz(slv[ib] | 0x80000000u) & 31;
-      const int sr = a.src_mode == kSrcPerPair ? sv[ib] * k + j0 : sv[ib];
-      srow[ib] = S + (size_t)sr * K;
-    }
-    const T* wrow[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const int r = rank_of_row<T>(rb, c16);
-      wrow[rb] = W + (size_t)(roff + (r < r_q ? r : r_q - 1)) * a.ldw;
-    }
-
-    f32x4 acc[NRB][RB];
-#pragma unroll
-    for (int ib = 0; ib < NRB; ++ib)
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) acc[ib][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // Main loop over this wave's full stages (U K-blocks each), register
-    // double-buffered: the next stage's loads are in flight while the
-    // matrix cores work on the current one.
-    struct Stage {
-      F sf[U][NRB];
-      F wf[U][RB];
-    };
-    auto load_stage = [&](int ks0, Stage& st) {
-#pragma unroll
-      for (int s = 0; s < U; ++s) {
-        const int kof = (ks0 + 4 * s) * KB + PER * g;
-#pragma unroll
-        for (int ib = 0; ib < NRB; ++ib) st.sf[s][ib] = Tr<T>::load(srow[ib] + kof);
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) st.wf[s][rb] = Tr<T>::load(wrow[rb] + kof);
-      }
-    };
-    auto mma_stage = [&](const Stage& st) {
-#pragma unroll
-      for (int s = 0; s < U; ++s)
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-          if (rb < nrb) {
-#pragma unroll
-            for (int ib = 0; ib < NRB; ++ib) acc[ib][rb] = Tr<T>::mma(st.wf[s][rb], st.sf[s][ib], acc[ib][rb]);
-          }
-    };
-    // stages of this wave: ks0 = wave + 4*U*i with ks0 + 4*(U-1) < nks_full
-    const int n_main = nks_full > wave + 4 * (U - 1) ? (nks_full - wave - 4 * (U - 1) + 4 * U - 1) / (4 * U) : 0;
-    {
-      Stage SA, SB;
-      if (n_main > 0) load_stage(wave, SA);
-      int i = 0;
-      for (; i + 1 < n_main; i += 2) {
-        load_stage(wave + 4 * U * (i + 1), SB);
-        mma_stage(SA);
-        if (i + 2 < n_main) load_stage(wave + 4 * U * (i + 2), SA);
-        mma_stage(SB);
-      }
-      if (i < n_main) mma_stage(SA);
-    }
-    int ks0 = wave + 4 * U * n_main;
-    for (; ks0 < nks; ks0 += 4) {  // leftover K-blocks of this wave (masked tail)
-      const int kof = ks0 * KB + PER * g;
-      const int nv = K - kof;
-      const int kc = nv > 0 ? kof : 0;
-      F sf[NRB], wf[RB];
-#pragma unroll
-      for (int ib = 0; ib < NRB; ++ib) sf[ib] = nv > 0 ? load_frag<T>(srow[ib] + kc, nv, true) : Tr<T>::zero();
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) wf[rb] = load_frag<T>(wrow[rb] + kc, nv, true);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-        if (rb < nrb) {
-#pragma unroll
-          for (int ib = 0; ib < NRB; ++ib) acc[ib][rb] = Tr<T>::mma(wf[rb], sf[ib], acc[ib][rb]);
-        }
-    }
-
-    // ---- partial sums meet in LDS; wave w finishes row block w % NRB
-    __syncthreads();
-#pragma unroll
-    for (int ib = 0; ib < NRB; ++ib)
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) red[wave][ib][rb][lane] = acc[ib][rb];
-    __syncthreads();
-    const int ib = wave % NRB;
-    if (wave >= NRB) continue;  // the other waves' row blocks are done by waves < NRB
-    const int u = u0 + 16 * ib + c16;
-    if (u0 + 16 * ib >= u_end) continue;  // wave-uniform
-    const bool valid = u < u_end;
-    const float s = a.alpha / (float)r_q;
-    f32x4 h[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      h[rb] = (((red[0][ib][rb][lane] + red[1][ib][rb][lane]) + red[2][ib][rb][lane]) +
-               red[3][ib][rb][lane]) * s;
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (rank_of_row<T>(rb, 4 * g + v) >= r_q) h[rb][v] = 0.f;
-    }
-    if (!valid) continue;
-    contract_store<T, RB>(a, q, lo, u, h);
-  }
-}
-
 // ------------------------------------------------------------- small batches
 //
 // Few rows (decode batches): latency bounds a tile, not bytes.  A block of 16
@@ -275,24 +112,25 @@ __global__ __launch_bounds__(kThreads) void contract_kernel(ContractArgs a) {
 // re-read the weights too often (1000 tokens, 564 tiles: a pass of the three
 // adapters takes 105 us with it, 86 without; 400 tokens, 216 tiles: 67 against 71)
 constexpr long kSmallTiles = 256;
-template <int RB>
+// NRB row blocks of 16 per tile, NWV waves
+template <int RB, int NRB_, int NWV_>
 struct CSmall {
-  static constexpr int NWV = 16;
-  static constexpr int SU = RB <= 4 ? 4 : RB == 8 ? 2 : 1;   // K-blocks in flight per wave
+  static constexpr int NRB = NRB_, NWV = NWV_;
+  static constexpr int SU = RB * NRB <= 4 ? 4 : RB * NRB <= 8 ? 2 : 1;   // K-blocks in flight per wave
   static constexpr int RRB = RB < 8 ? RB : 8;                // rank blocks per reduction pass
 };
 
-template <typename T, int RB>
-__global__ __launch_bounds__(64 * CSmall<RB>::NWV) void contract_small_kernel(ContractArgs a) {
+template <typename T, int RB, int NRB, int NWV>
+__global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a) {
   using F = typename Tr<T>::frag;
-  using G = CSmall<RB>;
-  constexpr int PER = Tr<T>::PER, KB = Tr<T>::KB, SU = G::SU, NWV = G::NWV;
+  using G = CSmall<RB, NRB, NWV>;
+  constexpr int PER = Tr<T>::PER, KB = Tr<T>::KB, SU = G::SU;
   __shared__ f32x4 red[NWV][G::RRB][64];
   const int n_keys = a.keys.n_keys;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, g = lane >> 4;
   int q, u0, u_end, lo;
-  if (!locate_tile(a.offsets, n_keys, 16, blockIdx.x, &q, &u0, &u_end,
+  if (!locate_tile(a.offsets, n_keys, 16 * NRB, blockIdx.x, &q, &u0, &u_end,
                    a.src_mode == kSrcPairList ? a.ppos : nullptr, &lo))
     return;
   q = __builtin_amdgcn_readfirstlane(q);
@@ -301,33 +139,40 @@ __global__ __launch_bounds__(64 * CSmall<RB>::NWV) void contract_small_kernel(Co
   const int K = a.K, k = a.k;
   // rows past the segment repeat its last row and weight rows past r_q the
   // last one (never stored, zeroed before any store): every load is unconditional
-  const int u = u0 + c16, uc = min(u, u_end - 1);
-  int sr;
-  if (a.src_mode == kSrcPairList) {
-    sr = a.plist[uc];
-  } else {
-    const int tok = a.row_token[uc];
-    const uint32_t sl = a.row_slots[uc];
-    sr = a.src_mode == kSrcPerPair ? tok * k + (__builtin_ctz(sl | 0x80000000u) & 31) : tok;
+  const T* srow[NRB];
+#pragma unroll
+  for (int ib = 0; ib < NRB; ++ib) {
+    const int uc = min(u0 + 16 * ib + c16, u_end - 1);
+    int sr;
+    if (a.src_mode == kSrcPairList) {
+      sr = a.plist[uc];
+    } else {
+      const int tok = a.row_token[uc];
+      const uint32_t sl = a.row_slots[uc];
+      sr = a.src_mode == kSrcPerPair ? tok * k + (__builtin_ctz(sl | 0x80000000u) & 31) : tok;
+    }
+    srow[ib] = static_cast<const T*>(a.src) + (size_t)sr * K;
   }
-  const T* srow = static_cast<const T*>(a.src) + (size_t)sr * K;
   const T* wrow[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int r = rank_of_row<T>(rb, c16);
     wrow[rb] = static_cast<const T*>(a.W) + (size_t)(roff + min(r, r_q - 1)) * a.ldw;
   }
-  f32x4 acc[RB];
+  f32x4 acc[NRB][RB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int ib = 0; ib < NRB; ++ib)
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) acc[ib][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int nks = (K + KB - 1) / KB;
   for (int ks = wave; ks < nks; ks += NWV * SU) {
-    F sf[SU], wf[SU][RB];
+    F sf[SU][NRB], wf[SU][RB];
     // K-blocks past the end repeat the last chunk of the row, with x zeroed
 #pragma unroll
     for (int s = 0; s < SU; ++s) {
       const int kof = (ks + NWV * s) * KB + PER * g, kc = min(kof, K - PER);
-      sf[s] = Tr<T>::load(srow + kc);
+#pragma unroll
+      for (int ib = 0; ib < NRB; ++ib) sf[s][ib] = Tr<T>::load(srow[ib] + kc);
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
         if (rb < nrb) wf[s][rb] = Tr<T>::load(wrow[rb] + kc);
@@ -335,46 +180,56 @@ __global__ __launch_bounds__(64 * CSmall<RB>::NWV) void contract_small_kernel(Co
 #pragma unroll
     for (int s = 0; s < SU; ++s) {
       const int kof = (ks + NWV * s) * KB + PER * g;
-      if (kof >= K) sf[s] = Tr<T>::zero();
       if (ks + NWV * s < nks) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-          if (rb < nrb) acc[rb] = Tr<T>::mma(wf[s][rb], sf[s], acc[rb]);
+        for (int ib = 0; ib < NRB; ++ib) {
+          if (kof >= K) sf[s][ib] = Tr<T>::zero();
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb)
+            if (rb < nrb) acc[ib][rb] = Tr<T>::mma(wf[s][rb], sf[s][ib], acc[ib][rb]);
+        }
       }
     }
   }
-  // partial sums: wave 0 adds them in wave order and finishes the tile
+  // partial sums, added in wave order; wave 0 finishes the rows
   const float s = a.alpha / (float)r_q;
-  f32x4 h[RB];
+  f32x4 h[NRB][RB];
 #pragma unroll
-  for (int p = 0; p < RB / G::RRB; ++p) {
-    if (p > 0) __syncthreads();
+  for (int ib = 0; ib < NRB; ++ib)
 #pragma unroll
-    for (int rb = 0; rb < G::RRB; ++rb) red[wave][rb][lane] = acc[p * G::RRB + rb];
-    __syncthreads();
-    // wave w sums rank block w's partials
-    if (wave < G::RRB) {
-      f32x4 t = red[0][wave][lane];
+    for (int p = 0; p < RB / G::RRB; ++p) {
+      if (ib + p > 0) __syncthreads();
 #pragma unroll
-      for (int w = 1; w < NWV; ++w) t += red[w][wave][lane];
-      red[0][wave][lane] = t;
+      for (int rb = 0; rb < G::RRB; ++rb) red[wave][rb][lane] = acc[ib][p * G::RRB + rb];
+      __syncthreads();
+      // wave w sums rank block w's partials
+      if (wave < G::RRB) {
+        f32x4 t = red[0][wave][lane];
+#pragma unroll
+        for (int w = 1; w < NWV; ++w) t += red[w][wave][lane];
+        red[0][wave][lane] = t;
+      }
+      __syncthreads();
+      if (wave == 0) {
+#pragma unroll
+        for (int rb = 0; rb < G::RRB; ++rb) h[ib][p * G::RRB + rb] = red[0][rb][lane] * s;
+      }
     }
-    __syncthreads();
-    if (wave == 0) {
+  if (wave != 0) return;
 #pragma unroll
-      for (int rb = 0; rb < G::RRB; ++rb) h[p * G::RRB + rb] = red[0][rb][lane] * s;
-    }
+  for (int ib = 0; ib < NRB; ++ib) {
+    const int u = u0 + 16 * ib + c16;
+    if (u >= u_end) continue;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (rank_of_row<T>(rb, 4 * g + v) >= r_q) h[ib][rb][v] = 0.f;
+    contract_store<T, RB>(a, q, lo, u, h[ib]);
   }
-  if (wave != 0 || u >= u_end) return;
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (rank_of_row<T>(rb, 4 * g + v) >= r_q) h[rb][v] = 0.f;
-  contract_store<T, RB>(a, q, lo, u, h);
 }
 
-// ------------------------------------------------------------- bf16 path
+// ------------------------------------------------------------- larger batches
 //
 // A block takes a tile of 64 rows of one key; wave w owns rows 16w .. 16w+15
 // for every rank over the whole contraction, so no cross-wave reduction is
@@ -395,20 +250,25 @@ __global__ __launch_bounds__(64 * CSmall<RB>::NWV) void contract_small_kernel(Co
 // LDS instead of sharing it with other blocks, a block takes one tile, found
 // without barriers.  OLMoE-like, 1000 tokens (188 tiles at most): a pass of
 // the three adapters 96 -> 86 us.
-template <int RB, int NWV, bool DEEP>
+template <typename T, int RB, int NWV, bool DEEP>
 struct CDma {
-  // contraction indices per stage and stages in LDS: ranks up to 32 take
-  // 128-column stages two deep (three blocks per CU); larger ranks, whose
-  // weight rows double the bytes of a stage, 64-column stages three deep
-  static constexpr int KC = RB <= 2 || (DEEP && RB == 4) ? 128 : 64;
-  static constexpr int NBUF = DEEP ? (RB == 4 ? 4 : 6) : RB <= 2 ? 2 : 3;
+  static constexpr bool F32 = sizeof(T) == 4;
+  // bytes of a row per stage and stages in LDS: ranks up to 32 take 256-byte
+  // stages two deep (three blocks per CU); larger ranks, whose weight rows
+  // double the bytes of a stage, 128-byte stages three deep (bf16).  fp32
+  // keeps 256 bytes (four K-blocks): it sums every fourth K-block apart, so
+  // that its chains of additions stay a quarter of the contraction.
+  static constexpr int ROWB = RB <= 2 || (DEEP && RB == 4) || (F32 && RB <= 8) ? 256 : 128;
+  static constexpr int NBUF = DEEP ? (ROWB == 256 && RB >= 4 ? (RB == 8 ? 3 : 4) : 6) : ROWB == 256 ? 2 : 3;
+  static constexpr int KC = ROWB / (int)sizeof(T);   // contraction indices per stage
+  static constexpr int NACC = F32 ? KC / Tr<T>::KB : 1;
   static constexpr int THREADS = 64 * NWV;       // NWV waves of 16 tile rows each
   static constexpr int ROWS = 16 * NWV;          // tile rows
-  static constexpr int CPR = KC / 8;             // 16-byte chunks per row piece
+  static constexpr int CPR = ROWB / 16;          // 16-byte chunks per row piece
   static constexpr int RPI = 64 / CPR;           // row pieces per copy instruction
-  static constexpr int SBYTES = ROWS * KC * 2;   // tile source rows x KC bf16
+  static constexpr int SBYTES = ROWS * ROWB;     // tile source rows
   static constexpr int WROWS = 16 * RB;
-  static constexpr int WBYTES = WROWS * KC * 2;  // weight rows x KC bf16
+  static constexpr int WBYTES = WROWS * ROWB;    // weight rows
   static constexpr int NS = 16 / RPI;            // source copies per wave per stage
   static constexpr int NW = (WROWS / RPI + NWV - 1) / NWV;   // weight copies per wave per stage (at most)
   static constexpr int LDS = NBUF * (SBYTES + WBYTES);
@@ -447,7 +307,7 @@ template <int RB, int NWV, bool DEEP>
 __device__ inline void row_sum_store(const ContractArgs& a, int q, const f32x4 (&acc)[RB], float s,
                                      float pw, int ua, int ub, int p0, int rfirst, int rstart,
                                      int rend, int rtok, float* hp) {
-  constexpr int RPS = CDma<RB, NWV, DEEP>::RPS;
+  constexpr int RPS = CDma<__bf16, RB, NWV, DEEP>::RPS;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c16 = lane & 15, g = lane >> 4;
   const int r_q = a.keys.rank[q], roff = a.keys.roff[q], R = a.keys.R;
@@ -498,14 +358,16 @@ __device__ inline void row_sum_store(const ContractArgs& a, int q, const f32x4 (
   }
 }
 
-template <int RB, int NWV, bool DEEP>
-__global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_dma_kernel(ContractArgs a) {
-  using G = CDma<RB, NWV, DEEP>;
-  constexpr int KC = G::KC, NBUF = G::NBUF, KB = Tr<__bf16>::KB;
+template <typename T, int RB, int NWV, bool DEEP>
+__global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP && sizeof(T) == 2 ? 2 : 1) void contract_dma_kernel(ContractArgs a) {
+  using G = CDma<T, RB, NWV, DEEP>;
+  using F = typename Tr<T>::frag;
+  constexpr int KC = G::KC, NBUF = G::NBUF, KB = Tr<T>::KB, PER = Tr<T>::PER, ROWB = G::ROWB;
   constexpr int CPR = G::CPR, RPI = G::RPI;
   // stage buffers: NBUF source stages, then NBUF weight stages; the row sums
   // reuse the whole area for the per-pair results
   __shared__ __attribute__((aligned(16))) char smem[G::LDS];
+  const uint32_t sbase = lds_addr(smem);
   char (*Sb)[G::SBYTES] = reinterpret_cast<char (*)[G::SBYTES]>(smem);
   char (*Wb)[G::WBYTES] = reinterpret_cast<char (*)[G::WBYTES]>(smem + NBUF * G::SBYTES);
   constexpr int TAB = DEEP ? 1 : kMaxKeys + 1;   // tile tables
@@ -517,7 +379,7 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
   const int n_keys = a.keys.n_keys;
   const int bucket = blockIdx.x % kXcds;
   const int K = a.K, k = a.k;
-  const bool rsum = a.row_sum != 0;   // implies kSrcPairList
+  const bool rsum = !G::F32 && a.row_sum != 0;   // implies kSrcPairList
   const int TS = contract_tile(a.row_sum, k, G::ROWS);
   const int32_t* seg_map = a.src_mode == kSrcPairList ? a.ppos : nullptr;
   int total = 1, stride = 1;
@@ -529,8 +391,8 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
   // wave-uniform values kept in scalar registers (uniform branches, no exec masks)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, g = lane >> 4;
-  const __bf16* S = static_cast<const __bf16*>(a.src);
-  const __bf16* W = static_cast<const __bf16*>(a.W);
+  const T* S = static_cast<const T*>(a.src);
+  const T* W = static_cast<const T*>(a.W);
   const int cpos = lane & (CPR - 1), crow = lane / CPR;   // 16-byte position / row inside a copy
 
   for (int idx = DEEP ? 0 : blockIdx.x / kXcds; idx < total; idx += stride) {
@@ -585,7 +447,7 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
 
     // source rows this lane copies (rows past the segment re-read the last
     // one) and the chunk of the row piece it copies
-    const __bf16* sptr[G::NS];
+    const T* sptr[G::NS];
     int scol[G::NS];
 #pragma unroll
     for (int i = 0; i < G::NS; ++i) {
@@ -598,15 +460,15 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
         sr = a.src_mode == kSrcPerPair ? tok * k + (__builtin_ctz(a.row_slots[uc] | 0x80000000u) & 31) : tok;
       }
       sptr[i] = S + (size_t)sr * K;
-      scol[i] = 8 * (cpos ^ ((16 * wave + RPI * i + crow) & (CPR - 1)));
+      scol[i] = PER * (cpos ^ ((16 * wave + RPI * i + crow) & (CPR - 1)));
     }
-    const __bf16* wptr[G::NW];
+    const T* wptr[G::NW];
     int wcol[G::NW];
 #pragma unroll
     for (int i = 0; i < G::NW; ++i) {
       const int rl = RPI * (wave * G::NW + i) + crow;  // weight row of the tile (rank)
       wptr[i] = W + (size_t)(roff + min(rl, r_q - 1)) * a.ldw;
-      wcol[i] = 8 * (cpos ^ w_swz<CPR>(rl));
+      wcol[i] = PER * (cpos ^ w_swz<CPR>(rl));
     }
     // copies of stage st (columns past K are clamped; masked at the reads)
     auto issue = [&](int st) {
@@ -615,20 +477,22 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
 #pragma unroll
       for (int i = 0; i < G::NS; ++i)
         if (i < ns)
-          dma16(sptr[i] + min(k0 + scol[i], K - 8),
-                __builtin_amdgcn_readfirstlane(lds_addr(&Sb[b][(16 * wave + RPI * i) * KC * 2])));
+          dma16(sptr[i] + min(k0 + scol[i], K - PER),
+                __builtin_amdgcn_readfirstlane(sbase + b * G::SBYTES + (16 * wave + RPI * i) * ROWB));
 #pragma unroll
       for (int i = 0; i < G::NW; ++i)
         if (i < nw)
-          dma16(wptr[i] + min(k0 + wcol[i], K - 8),
-                __builtin_amdgcn_readfirstlane(lds_addr(&Wb[b][RPI * (wave * G::NW + i) * KC * 2])));
+          dma16(wptr[i] + min(k0 + wcol[i], K - PER),
+                __builtin_amdgcn_readfirstlane(sbase + NBUF * G::SBYTES + b * G::WBYTES + RPI * (wave * G::NW + i) * ROWB));
     };
     const int per_stage = ns + nw;   // copies per stage of this wave
 
     __syncthreads();  // the previous tile is done with the buffers
-    f32x4 acc[RB];
+    f32x4 acc[G::NACC][RB];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int x = 0; x < G::NACC; ++x)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) acc[x][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int p = 0; p < NBUF - 1; ++p)
       if (p < nst) issue(p);
@@ -639,49 +503,66 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
       __syncthreads();
       if (st + NBUF - 1 < nst) issue(st + NBUF - 1);
     };
-    // K-block kb of stage st; the ragged form masks the indices past the
-    // block's range
-    auto kblock = [&](int st, int kb, bool ragged) {
+    // K-block kb of stage st for the first E rank blocks; the ragged form
+    // masks the indices past the block's range
+    auto kblock = [&](auto e_c, int st, int kb, bool ragged) {
+      constexpr int E = decltype(e_c)::value;
       const int b = st % NBUF;
       const int kk = st * KC + kb * KB;
       const int chunk = kb * 4 + g;
       const int rl = 16 * wave + c16;
-      bf16x8 sf = *reinterpret_cast<const bf16x8*>(&Sb[b][rl * KC * 2 + ((chunk ^ (rl & (CPR - 1))) << 4)]);
+      F sf = *reinterpret_cast<const F*>(&Sb[b][rl * ROWB + ((chunk ^ (rl & (CPR - 1))) << 4)]);
       if (ragged) {
-        const int nv = K - (kk + 8 * g);
+        const int nv = K - (kk + PER * g);
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (e >= nv) sf[e] = (__bf16)0.f;
+        for (int e = 0; e < PER; ++e)
+          if (e >= nv) sf[e] = (T)0.f;
       }
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
+      for (int rb = 0; rb < E; ++rb) {
         // weight rows at or past r_q were not copied: their results are zeroed below
-        const int wr = rank_of_row<__bf16>(rb, c16);
-        const bf16x8 wf = *reinterpret_cast<const bf16x8*>(&Wb[b][wr * KC * 2 + ((chunk ^ w_swz<CPR>(wr)) << 4)]);
-        acc[rb] = Tr<__bf16>::mma(wf, sf, acc[rb]);   // D[rank][row]
+        const int wr = rank_of_row<T>(rb, c16);
+        const F wf = *reinterpret_cast<const F*>(&Wb[b][wr * ROWB + ((chunk ^ w_swz<CPR>(wr)) << 4)]);
+        acc[kb % G::NACC][rb] = Tr<T>::mma(wf, sf, acc[kb % G::NACC][rb]);   // D[rank][row]
       }
     };
     // full stages: a loop with no branch around the matrix work (a branch
     // there made the compiler copy the accumulators every stage)
     const int nst_full = K / KC;
-    for (int st = 0; st < nst_full; ++st) {
-      begin_stage(st);
+    auto contract_all = [&](auto e_c) {
+      for (int st = 0; st < nst_full; ++st) {
+        begin_stage(st);
 #pragma unroll
-      for (int kb = 0; kb < KC / KB; ++kb) kblock(st, kb, false);
-    }
-    if (nst_full < nst) {   // block-uniform: the last, partial stage
-      const int st = nst_full;
-      begin_stage(st);
-#pragma unroll
-      for (int kb = 0; kb < KC / KB; ++kb) {
-        const int kk = st * KC + kb * KB;
-        if (kk < K) kblock(st, kb, kk + KB > K);
+        for (int kb = 0; kb < KC / KB; ++kb) kblock(e_c, st, kb, false);
       }
+      if (nst_full < nst) {   // block-uniform: the last, partial stage
+        const int st = nst_full;
+        begin_stage(st);
+#pragma unroll
+        for (int kb = 0; kb < KC / KB; ++kb) {
+          const int kk = st * KC + kb * KB;
+          if (kk < K) kblock(e_c, st, kb, kk + KB > K);
+        }
+      }
+    };
+    // fp32 matrix work is 16 times dearer than bf16's: keys of small rank in
+    // a call of larger ones leave out the rank blocks that they don't have
+    const int nrb = (r_q + 15) / 16;
+    if constexpr (G::F32 && RB >= 4) {
+      if (nrb <= RB / 4) contract_all(std::integral_constant<int, RB / 4>{});
+      else if (nrb <= RB / 2) contract_all(std::integral_constant<int, RB / 2>{});
+      else contract_all(std::integral_constant<int, RB>{});
+    } else {
+      contract_all(std::integral_constant<int, RB>{});
     }
 
     const float s = a.alpha / (float)r_q;
+#pragma unroll
+    for (int x = 1; x < G::NACC; ++x)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) acc[0][rb] += acc[x][rb];
     if (rsum) {
-      row_sum_store<RB, NWV, DEEP>(a, q, acc, s, pw, ua, ub, u0, rfirst, rstart, rend, rtok,
+      row_sum_store<RB, NWV, DEEP>(a, q, acc[0], s, pw, ua, ub, u0, rfirst, rstart, rend, rtok,
                              reinterpret_cast<float*>(smem));
       continue;
     }
@@ -690,24 +571,40 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
     f32x4 h[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      h[rb] = acc[rb] * s;
+      h[rb] = acc[0][rb] * s;
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        if (rank_of_row<__bf16>(rb, 4 * g + v) >= r_q) h[rb][v] = 0.f;
+        if (rank_of_row<T>(rb, 4 * g + v) >= r_q) h[rb][v] = 0.f;
     }
-    contract_store<__bf16, RB>(a, q, lo, u, h);
+    contract_store<T, RB>(a, q, lo, u, h);
   }
 }
 
-template <int RB, int NWV>
-hipError_t launch_contract_dma(const ContractArgs& a, long P, hipStream_t stream) {
-  using G = CDma<RB, NWV, false>;
+template <typename T, int RB>
+hipError_t launch_contract_rb(const ContractArgs& a, long P, hipStream_t stream) {
+  constexpr int NWV = 4;
+  using G = CDma<T, RB, NWV, false>;
+  const long n16 = P > 0 ? (P + 15) / 16 + a.keys.n_keys : 0;   // tiles of 16 rows, at most
+  if (n16 > 0 && n16 <= kSmallTiles && !a.row_sum) {
+    contract_small_kernel<T, RB, 1, 16><<<(int)n16, 64 * 16, 0, stream>>>(a);
+    return hipGetLastError();
+  }
+  // fp32 at ranks up to 64, whose matrix work fills a tile: tiles of 32 rows
+  // and four waves spread it over more blocks than the 64-row ones (OLMoE-like,
+  // 1999 tokens: 45 -> 27 us a call at rank 8, 76 -> 47 us at d 2048; group
+  // ranks up to 64 49 -> 36 us backward, level forward; 16-row tiles re-read
+  // the weights too often there, 69 us)
+  if constexpr (G::F32 && RB <= 4) {
+    const long n32 = P > 0 ? (P + 31) / 32 + a.keys.n_keys : 0;
+    if (n32 > 0) contract_small_kernel<T, RB, 2, 4><<<(int)n32, 64 * 4, 0, stream>>>(a);
+    return hipGetLastError();
+  }
   const int TS = contract_tile(a.row_sum, a.k, G::ROWS);
   const long tiles = P > 0 ? (P + TS - 1) / TS + a.keys.n_keys : 0;   // at most
   if constexpr (RB <= 8) {
     // one block per CU and one tile per block: see DEEP
     if (tiles > 0 && tiles <= device_cu_count()) {
-      contract_dma_kernel<RB, NWV, true><<<(int)tiles, G::THREADS, 0, stream>>>(a);
+      contract_dma_kernel<T, RB, NWV, true><<<(int)tiles, G::THREADS, 0, stream>>>(a);
       return hipGetLastError();
     }
   }
@@ -715,26 +612,7 @@ hipError_t launch_contract_dma(const ContractArgs& a, long P, hipStream_t stream
   const long pb = P > 0 ? tiles / kXcds + a.keys.n_keys : 0;
   const long cap = (long)G::BLOCKS_PER_CU * device_cu_count() / kXcds;
   const int grid = (int)(pb < cap ? pb : cap) * kXcds;
-  if (grid > 0) contract_dma_kernel<RB, NWV, false><<<grid, G::THREADS, 0, stream>>>(a);
-  return hipGetLastError();
-}
-
-template <typename T, int RB>
-hipError_t launch_contract_rb(const ContractArgs& a, long P, hipStream_t stream) {
-  const long small_tiles = P > 0 ? (P + 15) / 16 + a.keys.n_keys : 0;   // at most
-  if (small_tiles > 0 && small_tiles <= kSmallTiles && !a.row_sum) {
-    contract_small_kernel<T, RB><<<(int)small_tiles, 64 * CSmall<RB>::NWV, 0, stream>>>(a);
-    return hipGetLastError();
-  }
-  constexpr int BM = 16 * CGeo<RB>::NRB;
-  // tiles per bucket <= (all tiles) / kXcds + n_keys
-  const long per_bucket = P > 0 ? ((P + BM - 1) / BM + a.keys.n_keys) / kXcds + a.keys.n_keys : 0;
-  if constexpr (std::is_same<T, __bf16>::value) {
-    return launch_contract_dma<RB, 4>(a, P, stream);
-  }
-  const long cap = 6L * device_cu_count() / kXcds;
-  const int grid = (int)(per_bucket < cap ? per_bucket : cap) * kXcds;
-  if (grid > 0) contract_kernel<T, RB><<<grid, kThreads, 0, stream>>>(a);
+  if (grid > 0) contract_dma_kernel<T, RB, NWV, false><<<grid, G::THREADS, 0, stream>>>(a);
   return hipGetLastError();
 }
 

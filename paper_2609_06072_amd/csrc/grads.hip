@@ -929,15 +929,11 @@ __global__ __launch_bounds__(kWThreads) void dh_reduce_wide_kernel(DhReduceArgs 
 
 // ----------------------------------------------------------------- fp32 path
 
-template <typename T>
-__device__ inline typename Tr<T>::frag load_masked(const T* p, int nvalid) {
-  typename Tr<T>::frag f = Tr<T>::load(p);
-#pragma unroll
-  for (int e = 0; e < Tr<T>::PER; ++e)
-    if (e >= nvalid) f[e] = (T)0.f;
-  return f;
-}
-
+// The small operand's slice of a stage goes through LDS with the L rows, its
+// loads a stage ahead: read per K-block from global memory by every wave, its
+// latency bounded the item (each of the 64 K-blocks of a chunk a round trip).
+// OLMoE-like shapes, 1999 tokens, group ranks 16 to 64: 172 -> 94 us a call,
+// rank 8 74 -> 59 us.
 template <int RB>
 __global__ __launch_bounds__(kThreads) void grad_reg_kernel(GradArgs a) {
   using F = f32x4;
@@ -948,8 +944,10 @@ __global__ __launch_bounds__(kThreads) void grad_reg_kernel(GradArgs a) {
   constexpr int NJ = kColBlk / PER;           // 16-byte column pieces (32)
   constexpr int NBLK = NI * NJ / kThreads;    // 4 x 4 blocks per thread (2)
   constexpr int TI = NI / 8;
-  constexpr int SLD = RPS + PER;              // LDS stride of a transposed column
+  constexpr int SLD = RPS + PER;              // LDS stride of a transposed column or rank
+  constexpr int SPT = RB * 16 * NI / kThreads;   // 16-byte pieces of the small operand per thread
   __shared__ __attribute__((aligned(16))) float Sl[kColBlk * SLD];
+  __shared__ __attribute__((aligned(16))) float Ss[RB * 16 * SLD];
   __shared__ int idx[kMaxSplit];
   __shared__ GradTable tb;
   build_grad_table(a, tb, idx);
@@ -1000,6 +998,29 @@ __global__ __launch_bounds__(kThreads) void grad_reg_kernel(GradArgs a) {
         }
       }
     };
+    // piece x of this thread: indices PER * (tid % NI) .. of rank tid / NI + 16 x
+    // (= rank block x); ranks past r_q and indices past the chunk are zeros
+    F sv[SPT];
+    const int si = PER * (tid % NI), sr = tid / NI;
+    auto load_small = [&](int st) {
+#pragma unroll
+      for (int x = 0; x < SPT; ++x)
+        if (x < nrb)
+          sv[x] = *reinterpret_cast<const F*>(S + (size_t)(roff + min(16 * x + sr, r_q - 1)) * a.ldh +
+                                              min(scol0 + st * RPS + si, hmax));
+    };
+    auto write_small = [&](int st) {
+      const int nv = it.nk - (st * RPS + si);
+#pragma unroll
+      for (int x = 0; x < SPT; ++x)
+        if (x < nrb) {
+          F o = sv[x];
+#pragma unroll
+          for (int e = 0; e < PER; ++e)
+            if (e >= nv) o[e] = 0.f;
+          *reinterpret_cast<F*>(&Ss[(16 * x + sr) * SLD + si]) = o;
+        }
+    };
     auto write_stage = [&](int st) {
 #pragma unroll
       for (int x = 0; x < NBLK; ++x) {
@@ -1016,25 +1037,26 @@ __global__ __launch_bounds__(kThreads) void grad_reg_kernel(GradArgs a) {
         }
       }
     };
-    if (nst > 0) load_stage(0);
+    if (nst > 0) {
+      load_stage(0);
+      load_small(0);
+    }
     for (int st = 0; st < nst; ++st) {
       write_stage(st);
+      write_small(st);
       __syncthreads();
-      if (st + 1 < nst) load_stage(st + 1);
+      if (st + 1 < nst) {
+        load_stage(st + 1);
+        load_small(st + 1);
+      }
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb) {
         const int ul = st * RPS + kb * KB;
         if (ul >= it.nk) break;
-        const int nv = it.nk - (ul + PER * g);
-        const long hc = min(scol0 + ul + PER * g, hmax);
         F tf[RB];
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          if (rb < nrb) {
-            const int rr = min(16 * rb + c16, r_q - 1);
-            tf[rb] = load_masked<float>(S + (size_t)(roff + rr) * a.ldh + hc, nv);
-          }
-        }
+        for (int rb = 0; rb < RB; ++rb)
+          if (rb < nrb) tf[rb] = *reinterpret_cast<const F*>(&Ss[(16 * rb + c16) * SLD + kb * KB + PER * g]);
 #pragma unroll
         for (int cbi = 0; cbi < 2; ++cbi) {
           const F sf = *reinterpret_cast<const F*>(&Sl[(32 * wave + 16 * cbi + c16) * SLD + kb * KB + PER * g]);
