@@ -7,29 +7,25 @@
 // one per pair for expert-wise LoRA), computed beforehand by the contract
 // kernel.  y is written once: the adapter's read-modify-write of y is gone.
 //
-// Tiles.  The rows of the expert routing (sorted by expert, then token) are
-// cut into tiles of BM rows of one expert; a block computes a BM x BN
-// output tile (GCfg).  The contraction runs over d_in (x rows against W_e rows, both
-// K-contiguous) and then over the adapter rank (h rows against B_q rows, also
-// K-contiguous), all into the same fp32 accumulators.
+// Three kernels, chosen by the average number of rows per expert (see
+// launch_moe_gemm): streaming (few rows, any type), medium tiles and large
+// tiles (bf16).  Each cuts the rows of the expert routing (sorted by expert,
+// then token) into tiles of one expert's rows; the contraction runs over d_in
+// (x rows against W_e rows, both contiguous along it) and over the adapter
+// rank (h rows against B_q rows, from registers), into the same fp32
+// accumulators.  The weight rows are the first MFMA operand, so a lane's
+// accumulator holds four consecutive output columns of one row.
 //
-// Data movement.  One K-block (64 bytes of every row: 32 bf16 or 16 fp32) per
-// stage; x and W_e pieces are copied global -> LDS directly
-// (global_load_lds_dwordx4), NBUF stages in LDS.  Within a stage a row's
-// four 16-byte chunks sit XOR-swizzled (g_swz), so the fragment reads of 16
-// consecutive rows hit distinct banks.  The adapter K-blocks (one
-// or two) are read straight into registers while the first stages are in
-// flight.
+// Medium tiles.  One K-block (64 bytes of every row) per stage; x and W_e
+// pieces are copied global -> LDS directly (global_load_lds_dwordx4), a row's
+// four 16-byte chunks XOR-swizzled (g_swz) so that the fragment reads of 16
+// consecutive rows hit distinct banks.  Wave (wy, wx) owns rows 64*wy .. +64
+// and columns 128*wx .. +128.
 //
-// Waves.  WM x WN waves over the tile: wave (wy, wx) owns rows 64*wy .. +64
-// and columns 128*wx .. +128, i.e. 4 x 8 blocks of 16 x 16.  The
-// weight rows are the first MFMA operand, so a lane's accumulator holds four
-// consecutive output columns of one row; the epilogue stages the tile in LDS
-// and writes y with 16-byte stores of whole row pieces.
-//
-// Block order.  Blocks are dealt to the 8 XCDs round-robin; block b takes
-// tile (b % 8) * ceil(n_tiles / 8) + b / 8, so each XCD walks a contiguous
-// run of tiles (expert-major): an expert's weight slices stay in one L2.
+// Block order of the medium and large tiles.  Blocks are dealt to the 8 XCDs
+// round-robin; block b takes tile (b % 8) * ceil(n_tiles / 8) + b / 8, so each
+// XCD walks a contiguous run of tiles (expert-major): an expert's weight
+// slices stay in one L2.
 #include <type_traits>
 
 #include "ace_device.hpp"
@@ -53,15 +49,9 @@ struct GCfg {
   static_assert((BM + BN) / 16 % NW == 0, "copies must split evenly over the waves");
   static_assert(THREADS >= BM, "one thread per tile row fills the row tables");
 };
-// Two launch shapes.  Experts with few rows each (the fine-grained MoEs):
-// 128-row x 256-column tiles, four waves, three stages (72 KB of LDS, two
-// blocks per CU), so that an expert's last tile wastes little.  Experts with
-// many rows (>= kBigRows on average): 256 x 256 tiles, eight waves, four
-// stages (128 KB, one block per CU): a third fewer bytes per flop through the
-// L2 and 1.5x the work covered by the copies in flight.
-using MoeSmall = GCfg<2, 2, 3>;
-using MoeBig = GCfg<4, 2, 4>;
-constexpr long kBigRows = 1024;
+// Medium tiles (bf16): 128 rows x 256 columns, four waves, three stages (72 KB
+// of LDS, two blocks per CU), so that an expert's last tile wastes little.
+using MoeMid = GCfg<2, 2, 3>;
 constexpr int kRowGroup = 8;
 
 // Epilogue passes over column slices so that the C tile [BM][BN/NH + pad]
@@ -634,32 +624,212 @@ __global__ __launch_bounds__(Large::THREADS, 1) void moe_gemm_large_kernel(MoeAr
   }
 }
 
-template <class C>
-hipError_t launch_moe_cfg(int dtype, MoeArgs a, long P, hipStream_t stream) {
+// ---------------------------------------------------------------- few rows per expert
+//
+// Decode batches: every active expert's weights are read for a handful of
+// rows, so HBM bounds the call and a block streams W.  It takes up to 16 NRB
+// rows of one expert and 64 columns; wave w owns 16 columns over the whole
+// contraction.  Stages of 256 bytes of the 64 W rows and of the x rows are
+// copied global -> LDS, two in LDS (three or four blocks per CU keep 60 to
+// 70 KB in flight); W goes through non-temporal, it is read once.
+// OLMoE-like, 48 tokens (three projections of 268 MB of weights): 231 -> 200 us
+// a pass against the 128-row tiles, W at 5.0 TB/s; without the non-temporal
+// policy 217 us.
+template <typename T, int NRB>
+struct MStream {
+  static constexpr int ROWB = 256, KC = ROWB / (int)sizeof(T), NBUF = 2;
+  static constexpr int BM = 16 * NRB, BN = 64, NS = 4;     // NS: 4-row W copies per wave and stage
+  static constexpr int WBYTES = BN * ROWB, STAGE = WBYTES + BM * ROWB;
+};
+
+template <typename T, int NRB>
+__global__ __launch_bounds__(256) void moe_stream_kernel(MoeArgs a) {
+  using C = MStream<T, NRB>;
+  using F = typename Tr<T>::frag;
+  constexpr int PER = Tr<T>::PER, KB = Tr<T>::KB, KC = C::KC, ROWB = C::ROWB, NBUF = C::NBUF;
+  __shared__ __attribute__((aligned(16))) char smem[NBUF * C::STAGE];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15, g = lane >> 4;
+  const int mt = blockIdx.x / a.nt, n0 = (blockIdx.x % a.nt) * C::BN;
+  int e, u0, u_end;
+  if (!locate_tile(a.offsets, a.E, C::BM, mt, &e, &u0, &u_end)) return;   // block-uniform
+  e = __builtin_amdgcn_readfirstlane(e);
+  const int d_in = a.d_in, d_out = a.d_out;
+  const T* X = static_cast<const T*>(a.x);
+  const T* Wt = static_cast<const T*>(a.W) + (size_t)e * d_out * d_in;
+  auto pair_of = [&](int u) {   // (rows past the segment: its last row)
+    const int uc = min(u, u_end - 1);
+    return a.row_token[uc] * a.k + (__builtin_ctz(a.row_slots[uc] | 0x80000000u) & 31);
+  };
+  // copies: lane l takes the chunk at position l & 15 of row l >> 4 of a
+  // 4-row copy; a row's chunk 0 sits at position row & 15
+  const int crow = lane >> 4, cpos = lane & 15;
+  const T* wsrc[C::NS];
+  const T* xsrc[NRB];
+  int wcol[C::NS], xcol[NRB];
+#pragma unroll
+  for (int i = 0; i < C::NS; ++i) {
+    const int row = 16 * wave + 4 * i + crow;
+    wsrc[i] = Wt + (size_t)min(n0 + row, d_out - 1) * d_in;
+    wcol[i] = PER * (cpos ^ (row & 15));
+  }
+#pragma unroll
+  for (int i = 0; i < NRB; ++i) {
+    const int row = 4 * (wave * NRB + i) + crow;
+    const int p = pair_of(u0 + row);
+    xsrc[i] = X + (size_t)(a.per_pair ? p : p / a.k) * d_in;
+    xcol[i] = PER * (cpos ^ (row & 15));
+  }
+  // x copies of this wave that hold rows of the tile
+  const int nx = min(NRB, max(0, (u_end - u0 + 3) / 4 - wave * NRB));
+  const int nst = (d_in + KC - 1) / KC;
+  const uint32_t sbase = lds_addr(smem);
+  auto issue = [&](int st) {   // columns past d_in repeat the row's last chunk (masked in x)
+    const uint32_t buf = sbase + (st % NBUF) * C::STAGE;
+    const int k0 = st * KC;
+#pragma unroll
+    for (int i = 0; i < C::NS; ++i)
+      dma16_nt(wsrc[i] + min(k0 + wcol[i], d_in - PER),
+               __builtin_amdgcn_readfirstlane(buf + (16 * wave + 4 * i) * ROWB));
+#pragma unroll
+    for (int i = 0; i < NRB; ++i)
+      if (i < nx)
+        dma16(xsrc[i] + min(k0 + xcol[i], d_in - PER),
+              __builtin_amdgcn_readfirstlane(buf + C::WBYTES + 4 * (wave * NRB + i) * ROWB));
+  };
+  f32x4 acc[NRB];
+#pragma unroll
+  for (int ib = 0; ib < NRB; ++ib) acc[ib] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int p = 0; p < NBUF - 1; ++p)
+    if (p < nst) issue(p);
+  auto begin_stage = [&](int st) {
+    wait_vmcnt_upto<(NBUF - 2) * (C::NS + NRB)>(min(NBUF - 2, nst - 1 - st) * (C::NS + nx));
+    __syncthreads();
+    if (st + NBUF - 1 < nst) issue(st + NBUF - 1);
+  };
+  auto kblock = [&](int st, int kb, bool ragged) {
+    const char* S = smem + (st % NBUF) * C::STAGE;
+    const int chunk = ((kb * 4 + g) ^ c16) << 4;   // rows 16 i + c16
+    const F wf = *reinterpret_cast<const F*>(S + (16 * wave + c16) * ROWB + chunk);
+#pragma unroll
+    for (int ib = 0; ib < NRB; ++ib) {
+      F xf = *reinterpret_cast<const F*>(S + C::WBYTES + (16 * ib + c16) * ROWB + chunk);
+      if (ragged && st * KC + kb * KB + PER * g >= d_in) xf = Tr<T>::zero();
+      acc[ib] = Tr<T>::mma(wf, xf, acc[ib]);   // D[column][row]
+    }
+  };
+  const int nst_full = d_in / KC;
+  for (int st = 0; st < nst_full; ++st) {
+    begin_stage(st);
+#pragma unroll
+    for (int kb = 0; kb < KC / KB; ++kb) kblock(st, kb, false);
+  }
+  if (nst_full < nst) {
+    begin_stage(nst_full);
+#pragma unroll
+    for (int kb = 0; kb < KC / KB; ++kb)
+      if (nst_full * KC + kb * KB < d_in) kblock(nst_full, kb, true);
+  }
+  // the adapter's K-blocks, then the rows of y
+  int orow[NRB];
+#pragma unroll
+  for (int ib = 0; ib < NRB; ++ib) {
+    const int u = u0 + 16 * ib + c16;
+    orow[ib] = u < u_end ? pair_of(u) : -1;
+  }
+  if (a.H) {
+    const int q = a.key_of[e];
+    const int r_q = a.keys.rank[q];
+    const T* Bq = static_cast<const T*>(a.B) + (size_t)d_out * a.keys.roff[q];
+    const T* Hm = static_cast<const T*>(a.H);
+    const bool bvec = (r_q % PER) == 0;
+    const int n = min(n0 + 16 * wave + c16, d_out - 1);
+    int hrow[NRB];
+#pragma unroll
+    for (int ib = 0; ib < NRB; ++ib) hrow[ib] = orow[ib] >= 0 ? a.h_row[orow[ib]] : -1;
+    for (int kb = 0; kb * KB < r_q; ++kb) {
+      const int rho = kb * KB + PER * g;
+      const F bf = load_frag<T>(Bq + (size_t)n * r_q + rho, r_q - rho, bvec);
+#pragma unroll
+      for (int ib = 0; ib < NRB; ++ib) {
+        const F hf = hrow[ib] >= 0 ? Tr<T>::load(Hm + (size_t)hrow[ib] * a.rpad + rho) : Tr<T>::zero();
+        acc[ib] = Tr<T>::mma(bf, hf, acc[ib]);
+      }
+    }
+  }
+  T* Y = static_cast<T*>(a.y);
+  const int col = n0 + 16 * wave + 4 * g;   // four columns, all inside d_out or none
+#pragma unroll
+  for (int ib = 0; ib < NRB; ++ib)
+    if (orow[ib] >= 0 && col < d_out) {
+      typedef __attribute__((ext_vector_type(4))) T T4;
+      const f32x4 v = acc[ib];
+      *reinterpret_cast<T4*>(Y + (size_t)orow[ib] * d_out + col) = T4{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+    }
+}
+
+template <typename T, int NRB>
+hipError_t launch_moe_stream(MoeArgs a, long P, hipStream_t stream) {
+  using C = MStream<T, NRB>;
   a.nt = (a.d_out + C::BN - 1) / C::BN;
-  const long max_tiles = ((P + C::BM - 1) / C::BM + a.E) * a.nt;
-  const long grid = (max_tiles + kXcds - 1) / kXcds * kXcds;
-  if (grid <= 0) return hipSuccess;
-  if (dtype == ACE_BF16) moe_gemm_kernel<__bf16, C><<<(int)grid, C::THREADS, 0, stream>>>(a);
-  else moe_gemm_kernel<float, C><<<(int)grid, C::THREADS, 0, stream>>>(a);
+  const long grid = ((P + C::BM - 1) / C::BM + a.E) * a.nt;
+  if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
+  if (grid > 0) moe_stream_kernel<T, NRB><<<(int)grid, 256, 0, stream>>>(a);
   return hipGetLastError();
 }
 
-}  // namespace
+hipError_t launch_moe_mid(MoeArgs a, long P, hipStream_t stream) {
+  using C = MoeMid;
+  a.nt = (a.d_out + C::BN - 1) / C::BN;
+  const long max_tiles = ((P + C::BM - 1) / C::BM + a.E) * a.nt;
+  const long grid = (max_tiles + kXcds - 1) / kXcds * kXcds;
+  if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
+  if (grid > 0) moe_gemm_kernel<__bf16, C><<<(int)grid, C::THREADS, 0, stream>>>(a);
+  return hipGetLastError();
+}
 
 hipError_t launch_moe_large(MoeArgs a, long P, hipStream_t stream) {
   a.nt = (a.d_out + Large::BN - 1) / Large::BN;
   const long max_tiles = ((P + Large::BM - 1) / Large::BM + a.E) * a.nt;
   const long grid = (max_tiles + kXcds - 1) / kXcds * kXcds;
+  if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
   if (a.d_in % (2 * Large::KC)) moe_gemm_large_kernel<true><<<(int)grid, Large::THREADS, 0, stream>>>(a);
   else moe_gemm_large_kernel<false><<<(int)grid, Large::THREADS, 0, stream>>>(a);
   return hipGetLastError();
 }
 
+}  // namespace
+
+// Which kernel, by the average number of rows per expert, P / E.  Passes of
+// the three projections in us (streaming with 16 / 32 / 64 rows, medium,
+// large), OLMoE-like shapes:
+//     6 rows  202 / 199 / 200, 231, 266       25 rows  264 / 233 / 245, 306, 288
+//    62 rows  435 / 362 / 302, 323, 430      125 rows  684 / 534 / 455, 341, 425
+//   250 rows  medium 477, large 457          512 rows  medium 680, large 643
+// Mixtral-like:
+//     8 rows  550 / 580 / 582, 717, 864       50 rows  1553 / 1074 / 708, 802, 886
+//   100 rows  4th 857, large 899              200 rows  medium 1296, large 947
+// fp32 has its matrix units' rate behind it in every tile, so the streaming
+// kernel stays ahead throughout (1024 x 2048, 16 experts; against the medium
+// tiles): 37 rows 187 (606), 100 rows 314 (615), 250 rows 608 (902), 1000
+// rows 2121 / 2078 with 32 / 64 rows (2286).
+constexpr long kStream16 = 8, kStream32 = 32, kStream64 = 64, kLargeRows = 192;
+constexpr long kStream32F32 = 512;
+
 hipError_t launch_moe_gemm(int dtype, const MoeArgs& a, long P, hipStream_t stream) {
-  if (dtype == ACE_BF16 && P >= 128 * a.E && 2L * (a.per_pair ? P : P / a.k) * a.d_in < (1L << 32)) return launch_moe_large(a, P, stream);
-  if (P >= kBigRows * a.E) return launch_moe_cfg<MoeBig>(dtype, a, P, stream);
-  return launch_moe_cfg<MoeSmall>(dtype, a, P, stream);
+  if (dtype == ACE_F32) {
+    if (P <= kStream16 * a.E) return launch_moe_stream<float, 1>(a, P, stream);
+    if (P <= kStream32F32 * a.E) return launch_moe_stream<float, 2>(a, P, stream);
+    return launch_moe_stream<float, 4>(a, P, stream);
+  }
+  if (P <= kStream16 * a.E) return launch_moe_stream<__bf16, 1>(a, P, stream);
+  if (P <= kStream32 * a.E) return launch_moe_stream<__bf16, 2>(a, P, stream);
+  if (P <= kStream64 * a.E) return launch_moe_stream<__bf16, 4>(a, P, stream);
+  // the large tiles' x rows are 32-bit byte offsets
+  const long x_rows = a.per_pair ? P : P / a.k;
+  if (P >= kLargeRows * a.E && 2 * x_rows * a.d_in < (1L << 32)) return launch_moe_large(a, P, stream);
+  return launch_moe_mid(a, P, stream);
 }
 
 }  // namespace ace
