@@ -32,6 +32,8 @@
 //              wave per pair, which also forms num_ii and num_jj and writes
 //              S_ij directly; otherwise one block per pair, then
 //   score   -- S_ij = num_ij / sqrt(num_ii num_jj); 0 when a norm is 0
+#include <type_traits>
+
 #include "ace_device.hpp"
 #include "ace_internal.hpp"
 
@@ -256,6 +258,137 @@ __global__ __launch_bounds__(kPThreads) void cka_project_kernel(CkaArgs a) {
 #pragma unroll
     for (int jc = 0; jc < 4; ++jc) {
       const int c = c0 + wc + 16 * jc + c16, n = n0 + wn + 16 * jn + 4 * g;
+      if (c < R && n < N) {
+        float* dst = a.Pt + (size_t)c * a.ldp + n;
+        if (n + 3 < N) {
+          *reinterpret_cast<f32x4*>(dst) = acc[jn][jc];
+        } else {
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (n + v < N) dst[v] = acc[jn][jc][v];
+        }
+      }
+    }
+}
+
+// bf16 inputs: PN probe rows x 256 adapter rows per block, four waves of
+// PN x 64, one block per CU, three stages of 128 bytes per row in LDS.  What
+// bounds it is the copies' latency (A's rows come from the L2, X's from HBM):
+// a stage's slot takes the copies of the third stage after it as soon as its
+// second K-block's fragments are in registers, so that two to three stages
+// (86 to 144 KB per CU) are in flight against one 40 KB stage per block
+// before.  PN comes in steps of 16 rows (launch_project): as many blocks as
+// CUs, not half as many again.  OLMoE-like, 10,000 probe rows: CKAPROJ
+template <int PN, bool RAGGED>
+__global__ __launch_bounds__(256, 1) void cka_project_wide_kernel(CkaArgs a) {
+  using F = bf16x8;
+  constexpr int KS = 64, RB = 128, NBUF = 3;       // indices and bytes of a row per stage
+  constexpr int JN = PN / 16;                       // 16-row probe blocks
+  constexpr int XI = PN / 8, AC = kPC / 8 / 4;      // X copies per stage, A copies per wave
+  constexpr int XC = (XI + 3) / 4;                  // X copies per wave, at most
+  constexpr int STAGE = (PN + kPC) * RB;
+  static_assert(PN % 16 == 0 && NBUF * STAGE <= 160 * 1024, "tile");
+  __shared__ __attribute__((aligned(16))) char sm[NBUF * STAGE];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15, g = lane >> 4;
+  const int n0 = blockIdx.x * PN, c0 = blockIdx.y * kPC;
+  const __bf16* X = static_cast<const __bf16*>(a.X);
+  const __bf16* A = static_cast<const __bf16*>(a.A);
+  const int N = a.N, R = a.R, d_in = a.d_in;
+  const int nst = (d_in + KS - 1) / KS;
+  // copies of 8 rows: X copies wave, wave + 4, ... (past the tile: the last
+  // one again); A rows 64 wave ..
+  const int crow = lane >> 3, cpos = lane & 7;
+  const __bf16* xsrc[XC];
+  const __bf16* asrc[AC];
+  int xch[XC], ach[AC];
+#pragma unroll
+  for (int i = 0; i < XC; ++i) {
+    const int r = 8 * min(wave + 4 * i, XI - 1) + crow;
+    xsrc[i] = X + (size_t)min(n0 + r, N - 1) * d_in;
+    xch[i] = 8 * (cpos ^ cka_sw(r));
+  }
+#pragma unroll
+  for (int i = 0; i < AC; ++i) {
+    const int r = 64 * wave + 8 * i + crow;
+    asrc[i] = A + (size_t)min(c0 + r, R - 1) * d_in;
+    ach[i] = 8 * (cpos ^ cka_sw(r));
+  }
+  const uint32_t sbase = lds_addr(sm);
+  // copy i of stage st (chunks past d_in repeat the row's last one, masked in
+  // x; stages past the last one repeat it into slots that nothing reads)
+  auto copy = [&](int st, int i) {
+    const uint32_t buf = sbase + (st % NBUF) * STAGE;
+    const int k0 = min(st, nst - 1) * KS;
+    if (i < XC)
+      dma16(xsrc[i] + min(k0 + xch[i], d_in - 8),
+            __builtin_amdgcn_readfirstlane(buf + 8 * min(wave + 4 * i, XI - 1) * RB));
+    else
+      dma16(asrc[i - XC] + min(k0 + ach[i - XC], d_in - 8),
+            __builtin_amdgcn_readfirstlane(buf + (PN + 64 * wave + 8 * (i - XC)) * RB));
+  };
+  const int sw = cka_sw(c16);   // rows 16 j + c16
+  auto frag = [&](int st, int kb, int row) {
+    return *reinterpret_cast<const F*>(sm + (st % NBUF) * STAGE + (row + c16) * RB + (((4 * kb + g) ^ sw) << 4));
+  };
+  f32x4 acc[JN][4];
+#pragma unroll
+  for (int i = 0; i < JN; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // K-block kb of stage st in (xc, ac): groups of four matrix instructions,
+  // between them the reads of the next K-block (sn, kn) and, with COPY, the
+  // copies of stage st + NBUF (one wave per SIMD: nothing else hides them)
+  auto kblock = [&](auto copy_c, int st, int kb, F (&xc)[JN], const F (&ac)[4], int sn, int kn,
+                    F (&xn)[JN], F (&an)[4]) {
+    constexpr bool COPY = decltype(copy_c)::value;
+    constexpr int CP = (XC + AC + JN - 1) / JN;
+    if (RAGGED && st * KS + 32 * kb + 8 * g >= d_in) {
+#pragma unroll
+      for (int j = 0; j < JN; ++j) xc[j] = Tr<__bf16>::zero();
+    }
+#pragma unroll
+    for (int jn = 0; jn < JN; ++jn) {
+      if (jn < 4) an[jn] = frag(sn, kn, PN + 64 * wave + 16 * jn);
+      xn[jn] = frag(sn, kn, 16 * jn);
+      if constexpr (COPY) {
+#pragma unroll
+        for (int i = jn * CP; i < (jn + 1) * CP; ++i)
+          if (i < XC + AC) copy(st + NBUF, i);
+      }
+#pragma unroll
+      for (int jc = 0; jc < 4; ++jc) mfma_acc(acc[jn][jc], xc[jn], ac[jc]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < NBUF; ++s)
+#pragma unroll
+    for (int i = 0; i < XC + AC; ++i) copy(s, i);
+  wait_vmcnt<(NBUF - 1) * (XC + AC)>();
+  __syncthreads();
+  F x0[JN], a0[4], x1[JN], a1[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) a0[j] = frag(0, 0, PN + 64 * wave + 16 * j);
+#pragma unroll
+  for (int j = 0; j < JN; ++j) x0[j] = frag(0, 0, 16 * j);
+  for (int st = 0; st < nst; ++st) {
+    kblock(std::false_type{}, st, 0, x0, a0, st, 1, x1, a1);
+    // stage st is in registers; stage st + 1 has landed once at most the
+    // copies of stage st + 2 are outstanding
+    wait_vmcnt<XC + AC>();
+    __syncthreads();   // (waits for this wave's LDS reads, then for every wave)
+    kblock(std::true_type{}, st, 1, x1, a1, st + 1, 0, x0, a0);
+  }
+  wait_vmcnt<0>();   // copies past the last stage
+  mfma_done();
+  __builtin_amdgcn_sched_barrier(0);
+  // acc[jn][jc] element v = P[n][c], n = n0 + 16 jn + 4 g + v, c = c0 + 64 wave + 16 jc + c16
+#pragma unroll
+  for (int jn = 0; jn < JN; ++jn)
+#pragma unroll
+    for (int jc = 0; jc < 4; ++jc) {
+      const int c = c0 + 64 * wave + 16 * jc + c16, n = n0 + 16 * jn + 4 * g;
       if (c < R && n < N) {
         float* dst = a.Pt + (size_t)c * a.ldp + n;
         if (n + 3 < N) {
@@ -730,6 +863,36 @@ __device__ void bgram_small(const CkaArgs& a, int e) {
   else bgram_small_t<float>(a, e);
 }
 
+template <int PN>
+void launch_project_wide(const CkaArgs& a, hipStream_t stream) {
+  const dim3 grid((a.N + PN - 1) / PN, (a.R + kPC - 1) / kPC);
+  if (a.d_in % 64) cka_project_wide_kernel<PN, true><<<grid, 256, 0, stream>>>(a);
+  else cka_project_wide_kernel<PN, false><<<grid, 256, 0, stream>>>(a);
+}
+
+// Probe rows per block: of 64, 80, 96, 112 and 128 the size with the least
+// rounds of blocks times bytes per block (the time of a block is its copies').
+void launch_project(const CkaArgs& a, hipStream_t stream) {
+  const long cy = (a.R + kPC - 1) / kPC, cus = device_cu_count();
+  int best = 0;
+  long cost = 0;
+  for (int pn = 64; pn <= 128; pn += 16) {
+    const long rounds = (((long)a.N + pn - 1) / pn * cy + cus - 1) / cus;
+    const long c = rounds * (pn + kPC);
+    if (!best || c < cost) {
+      best = pn;
+      cost = c;
+    }
+  }
+  switch (best) {
+    case 64: return launch_project_wide<64>(a, stream);
+    case 80: return launch_project_wide<80>(a, stream);
+    case 96: return launch_project_wide<96>(a, stream);
+    case 112: return launch_project_wide<112>(a, stream);
+    default: return launch_project_wide<128>(a, stream);
+  }
+}
+
 template <typename T>
 hipError_t launch_cka_t(const CkaProblem& p, void* ws, hipStream_t stream) {
   const CkaLayout L = cka_layout(p.N, p.d_out, p.E, p.r);
@@ -760,8 +923,12 @@ hipError_t launch_cka_t(const CkaProblem& p, void* ws, hipStream_t stream) {
   a.bf16 = p.dtype == ACE_BF16 ? 1 : 0;
   const int R = a.R;
   if (p.N > 0) {
-    dim3 grid((p.N + kPN - 1) / kPN, (R + kPC - 1) / kPC);
-    cka_project_kernel<T, kPN, kPBuf><<<grid, kPThreads, 0, stream>>>(a);
+    if (p.dtype == ACE_BF16) {
+      launch_project(a, stream);
+    } else {
+      const dim3 grid((p.N + kPN - 1) / kPN, (R + kPC - 1) / kPC);
+      cka_project_kernel<float, kPN, kPBuf><<<grid, kPThreads, 0, stream>>>(a);
+    }
   }
   if (p.dtype == ACE_BF16)
     cka_mean_kernel<true><<<R, kThreads, 0, stream>>>(a);

@@ -375,16 +375,6 @@ __device__ inline bool locate_key(const int32_t* offsets, int n_keys, int BM, in
   return true;
 }
 
-// D += A B with D held in accumulation registers: with 256 of them the
-// compiler's own choice moves accumulators between register files inside the
-// loop.  The compiler's hazard tables don't see the instruction: s_nop covers
-// operands written by a vector instruction right before it, and mfma_done()
-// stands between the last one and the first read of an accumulator.
-__device__ inline void mfma_acc(f32x4& d, bf16x8 a, bf16x8 b) {
-  asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
-}
-__device__ inline void mfma_done() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
-
 // RAGGED: d_in is no multiple of two stages; the chunks past it are zeroed in
 // the fragments.
 template <bool RAGGED>
