@@ -12,10 +12,9 @@
 // exact up to rounding; no N x d_out matrix is ever formed.
 //
 // Launches (all deterministic):
-//   project -- Pt = A X^T, [R][ldp] fp32: a 64 x 256-tile MFMA GEMM over
-//              K = d_in (eight waves), operands copied global -> LDS
-//              directly, two stages of 128 bytes per row in LDS (128 x 256
-//              tiles with two or three stages measured no faster)
+//   project -- Pt = A X^T, [R][ldp] fp32: an MFMA GEMM over K = d_in,
+//              operands copied global -> LDS directly; bf16 tiles of 64 to
+//              128 probe rows x 256 adapter rows, fp32 64 x 256
 //   mean    -- the probe mean of every row of Pt; bf16 inputs: also the
 //              centred rows split as v = hi + lo (both bf16, |lo| <= 2^-9 |v|)
 //   gram    -- partial M over chunks of the probe (at least kGK rows): upper-triangle tiles
@@ -278,7 +277,9 @@ __global__ __launch_bounds__(kPThreads) void cka_project_kernel(CkaArgs a) {
 // second K-block's fragments are in registers, so that two to three stages
 // (86 to 144 KB per CU) are in flight against one 40 KB stage per block
 // before.  PN comes in steps of 16 rows (launch_project): as many blocks as
-// CUs, not half as many again.  OLMoE-like, 10,000 probe rows: CKAPROJ
+// CUs, not half as many again.  OLMoE-like, 10,000 probe rows:
+// 42 -> 32 us (the same tiles with every read and copy of a stage ahead of
+// its matrix work: 36 us).
 template <int PN, bool RAGGED>
 __global__ __launch_bounds__(256, 1) void cka_project_wide_kernel(CkaArgs a) {
   using F = bf16x8;
@@ -407,42 +408,68 @@ __global__ __launch_bounds__(256, 1) void cka_project_wide_kernel(CkaArgs a) {
 // Block c: the probe mean of Pt row c; with SPLIT, also the centred row split
 // as v = hi + lo in bf16 (hi = v rounded, lo = the remainder rounded), zero
 // from N up to ldp, so the Gram reads ready matrix-core operands.
+// Rows of up to kThreads * 4 * kMeanRegs probe rows stay in registers between
+// the sum and the split: one round trip instead of two (10,000 rows:
+// 10.8 -> 9.2 us).
+constexpr int kMeanRegs = 16;
 template <bool SPLIT>
 __global__ __launch_bounds__(kThreads) void cka_mean_kernel(CkaArgs a) {
-  __shared__ float red[kThreads];
+  __shared__ float red[kThreads / 64];
   // ldp is a multiple of 32: whole 16-byte pieces, entries past N masked
   const f32x4* row = reinterpret_cast<const f32x4*>(a.Pt + (size_t)blockIdx.x * a.ldp);
-  const int n4 = (a.N + 3) / 4;
+  const int n4 = (a.N + 3) / 4, last = max(n4 - 1, 0);
+  const bool regs = n4 <= kThreads * kMeanRegs;   // block-uniform
+  f32x4 v[kMeanRegs];
   float s = 0.f;
-#pragma unroll 4
-  for (int i = threadIdx.x; i < n4; i += kThreads) {
-    const f32x4 v = row[i];
+  auto add = [&](int i, f32x4 x) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s += 4 * i + e < a.N ? v[e] : 0.f;
+    for (int e = 0; e < 4; ++e) s += 4 * i + e < a.N ? x[e] : 0.f;
+  };
+  if (regs) {
+#pragma unroll
+    for (int j = 0; j < kMeanRegs; ++j)
+      if (j * kThreads < n4) v[j] = row[min(j * kThreads + (int)threadIdx.x, last)];
+#pragma unroll
+    for (int j = 0; j < kMeanRegs; ++j)
+      if (j * kThreads < n4) add(j * kThreads + threadIdx.x, v[j]);
+  } else {
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n4; i += kThreads) add(i, row[i]);
   }
-  red[threadIdx.x] = s;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
-  for (int w = kThreads / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  const float mean = a.N > 0 ? red[0] / (float)a.N : 0.f;
+  const float mean = a.N > 0 ? ((red[0] + red[1]) + (red[2] + red[3])) / (float)a.N : 0.f;
   if (threadIdx.x == 0) a.mean[blockIdx.x] = mean;
   if constexpr (SPLIT) {
     bf16x4* hi = reinterpret_cast<bf16x4*>(a.Phi + (size_t)blockIdx.x * a.ldp);
     bf16x4* lo = reinterpret_cast<bf16x4*>(a.Plo + (size_t)blockIdx.x * a.ldp);
-#pragma unroll 4
-    for (int i = threadIdx.x; i < a.ldp / 4; i += kThreads) {
-      const f32x4 v = row[min(i, max(n4 - 1, 0))];
+    auto split = [&](int i, f32x4 x) {
       bf16x4 h, l;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float c = 4 * i + e < a.N ? v[e] - mean : 0.f;
+        const float c = 4 * i + e < a.N ? x[e] - mean : 0.f;
         h[e] = (__bf16)c;
         l[e] = (__bf16)(c - (float)h[e]);
       }
       hi[i] = h;
       lo[i] = l;
+    };
+    const int ld4 = a.ldp / 4;   // at most 7 pieces past n4
+    if (regs) {
+#pragma unroll
+      for (int j = 0; j < kMeanRegs; ++j) {
+        const int i = j * kThreads + threadIdx.x;
+        if (j * kThreads < n4 && i < ld4) split(i, v[j]);
+      }
+      // the padding's pieces past the last whole batch are zeros
+      const int done = (n4 + kThreads - 1) / kThreads * kThreads;
+      const int i = done + threadIdx.x;
+      if (i < ld4) split(i, f32x4{0.f, 0.f, 0.f, 0.f});
+    } else {
+#pragma unroll 4
+      for (int i = threadIdx.x; i < ld4; i += kThreads) split(i, row[min(i, last)]);
     }
   }
 }
