@@ -8,6 +8,7 @@ no fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Sequence
 
@@ -114,8 +115,14 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr() or None
 
 
+# the current stream's handle without building a Stream object (2.8 us a call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device()) or None
         stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
 
@@ -144,10 +151,10 @@ def _want(name: str, t, numel: Optional[int] = None, dtype=None, device=None,
         raise ValueError(f"{name} is on {t.device}, expected {device}")
 
 
-def _check_lora_args(x, A, B, ranks: Sequence[int], routing: "Routing", d_out: int,
+def _check_lora_args(x, A, B, R: int, n_keys: int, routing: "Routing", d_out: int,
                      input_mode: int, pair_w, y=None, dy=None, dx=None, dA=None, dB=None) -> None:
+    """R: total rank of the call's n_keys adapters."""
     T, k = routing.c.T, routing.c.k
-    R = int(sum(int(r) for r in ranks))
     dt, dev = A.dtype, A.device
     if A.dim() != 2 or A.shape[0] != R:
         raise ValueError(f"A must be [R={R}, d_in], got {tuple(A.shape)}")
@@ -164,8 +171,8 @@ def _check_lora_args(x, A, B, ranks: Sequence[int], routing: "Routing", d_out: i
         _want("dx", dx, rows_in * d_in, dt, dev)
         _want("dA", dA, R * d_in, torch.float32, dev)
         _want("dB", dB, R * d_out, torch.float32, dev)
-    if routing.n_keys != len(ranks):
-        raise ValueError(f"routing has {routing.n_keys} keys, the call has {len(ranks)}")
+    if routing.n_keys != n_keys:
+        raise ValueError(f"routing has {routing.n_keys} keys, the call has {n_keys}")
 
 
 def ace_workspace_bytes(op: int, T: int, k: int, d_in: int, d_out: int, n_keys: int,
@@ -281,9 +288,11 @@ def ace_routing_check(routing: Routing, stream=None) -> int:
     return int(n.value)
 
 
-def _ranks_arg(ranks: Sequence[int]):
-    arr = (ctypes.c_int32 * len(ranks))(*[int(r) for r in ranks])
-    return arr
+@functools.lru_cache(maxsize=256)
+def _rank_table(ranks: tuple):
+    """(C array, total, largest) of a rank list, kept by value: a layer passes
+    the same few lists on every call, and the library only reads them."""
+    return (ctypes.c_int32 * len(ranks))(*ranks), sum(ranks), max(ranks, default=0)
 
 
 def _fwd_ws(ws, T, k, d_in, d_out, n_keys, r_max, device):
@@ -298,9 +307,9 @@ def ace_grouped_lora_fwd(x, A, B, group_rank: Sequence[int], alpha: float, routi
                          stream=None) -> None:
     T, k = routing.c.T, routing.c.k
     d_in, d_out = A.shape[1], y.shape[1]
-    _check_lora_args(x, A, B, group_rank, routing, d_out, input_mode, pair_w, y=y)
-    ranks = _ranks_arg(group_rank)
-    ws = _fwd_ws(ws, T, k, d_in, d_out, len(group_rank), max(group_rank), A.device)
+    ranks, R, r_max = _rank_table(tuple(map(int, group_rank)))
+    _check_lora_args(x, A, B, R, len(group_rank), routing, d_out, input_mode, pair_w, y=y)
+    ws = _fwd_ws(ws, T, k, d_in, d_out, len(group_rank), r_max, A.device)
     _check(_lib.ace_grouped_lora_fwd(_dtype(x), input_mode, T, k, d_in, d_out, len(group_rank),
                                      ranks, alpha, _ptr(x), _ptr(A), _ptr(B), _ptr(pair_w),
                                      ctypes.byref(routing.c), _ptr(y), _ptr(ws),
@@ -315,11 +324,11 @@ def ace_grouped_lora_bwd(x, A, B, group_rank: Sequence[int], alpha: float, routi
     (the backward then reuses the forward's h instead of recomputing it)."""
     T, k = routing.c.T, routing.c.k
     d_in, d_out = A.shape[1], dy.shape[1]
-    _check_lora_args(x, A, B, group_rank, routing, d_out, input_mode, pair_w, dy=dy, dx=dx,
+    ranks, R, r_max = _rank_table(tuple(map(int, group_rank)))
+    _check_lora_args(x, A, B, R, len(group_rank), routing, d_out, input_mode, pair_w, dy=dy, dx=dx,
                      dA=dA, dB=dB)
-    ranks = _ranks_arg(group_rank)
     if ws is None:
-        need = ace_workspace_bytes(ACE_OP_BWD, T, k, d_in, d_out, len(group_rank), max(group_rank))
+        need = ace_workspace_bytes(ACE_OP_BWD, T, k, d_in, d_out, len(group_rank), r_max)
         ws = torch.empty(max(need, 256), dtype=torch.uint8, device=A.device)
     _check(_lib.ace_grouped_lora_bwd(_dtype(A), input_mode, T, k, d_in, d_out, len(group_rank),
                                      ranks, alpha, _ptr(x), _ptr(A), _ptr(B), _ptr(pair_w),
@@ -333,7 +342,7 @@ def ace_expertwise_lora_fwd(x, A, B, E: int, rank: int, alpha: float, routing: R
                             stream=None) -> None:
     T, k = routing.c.T, routing.c.k
     d_in, d_out = A.shape[1], y.shape[1]
-    _check_lora_args(x, A, B, [rank] * E, routing, d_out, input_mode, pair_w, y=y)
+    _check_lora_args(x, A, B, int(rank) * E, E, routing, d_out, input_mode, pair_w, y=y)
     ws = _fwd_ws(ws, T, k, d_in, d_out, E, rank, A.device)
     _check(_lib.ace_expertwise_lora_fwd(_dtype(x), input_mode, T, k, d_in, d_out, E, rank, alpha,
                                         _ptr(x), _ptr(A), _ptr(B), _ptr(pair_w),
@@ -347,7 +356,7 @@ def ace_expertwise_lora_bwd(x, A, B, E: int, rank: int, alpha: float, routing: R
                             stream=None, h_fwd=None) -> None:
     T, k = routing.c.T, routing.c.k
     d_in, d_out = A.shape[1], dy.shape[1]
-    _check_lora_args(x, A, B, [rank] * E, routing, d_out, input_mode, pair_w, dy=dy, dx=dx,
+    _check_lora_args(x, A, B, int(rank) * E, E, routing, d_out, input_mode, pair_w, dy=dy, dx=dx,
                      dA=dA, dB=dB)
     if ws is None:
         need = ace_workspace_bytes(ACE_OP_BWD, T, k, d_in, d_out, E, rank)
@@ -454,10 +463,11 @@ def ace_moe_lora_fwd(x, W, expert_routing: Routing, y, key_rank: Optional[Sequen
     T, k = expert_routing.c.T, expert_routing.c.k
     E, d_out, d_in = W.shape
     n_keys = 0 if key_rank is None else len(key_rank)
-    ranks = _ranks_arg(key_rank) if n_keys else None
-    ekey = (ctypes.c_int32 * E)(*[int(v) for v in expert_key]) if n_keys else None
+    ranks = ekey = None
     if n_keys:
-        ws = _fwd_ws(ws, T, k, d_in, d_out, n_keys, max(key_rank), x.device)
+        ranks, _, r_max = _rank_table(tuple(map(int, key_rank)))
+        ekey = (ctypes.c_int32 * E)(*[int(v) for v in expert_key])
+        ws = _fwd_ws(ws, T, k, d_in, d_out, n_keys, r_max, x.device)
     _check(_lib.ace_moe_lora_fwd(_dtype(x), input_mode, T, k, d_in, d_out, E, _ptr(x), _ptr(W),
                                  ctypes.byref(expert_routing.c), n_keys, ranks, ekey, alpha,
                                  _ptr(A), _ptr(B),
