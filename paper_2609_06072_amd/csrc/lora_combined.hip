@@ -8,20 +8,26 @@
 // that differs per routed pair.  Since A_q is linear the launches evaluate
 // h_u = s_q A_q z_u as sum_p w_p (s_q A_q x_p):
 //
-// Forward (h_p per pair position stays in the workspace for the backward):
+// Forward (h stays in the workspace for the backward: the dense h rows for
+// bf16, h_p per pair position for fp32):
 //   prep      -- B^T rows [R][d_out] (matrix-core GEMM operand) or B
 //                re-strided to [d_out][R] (register GEMM); zero the dense
 //                per-token h rows.
-//   contract  -- h_p = s_q A_q x_p for every routed pair, in pair order.
-//   combine   -- h_u = sum_{p in u} w_p h_p into the dense rows Hd[t][roff_q..].
+//   contract  -- h_p = s_q A_q x_p for every routed pair, in pair order; bf16:
+//                its epilogue sums h_u = sum_{p in u} w_p h_p in fp32 and stores
+//                the dense rows Hd[t][roff_q..] (a launch of its own over the
+//                stored h_p cost 15.6 us beside the contraction's 36 at the
+//                Qwen-like shape).
+//   combine   -- fp32: h_u from the stored h_p into the dense rows.
 //   GEMM      -- out[t] += Hd[t] B^T over K = R (inactive groups hold zeros).
 // Backward, with G_t = dOut[t] (every row of token t sees the same gradient):
 //   dB_q = sum_u G_t h_u^T                (rows of q)
 //   dH_u = s_q B_q^T G_t
 //   dA_q = sum_p (w_p dH_{u(p)}) x_p^T    (pairs of q)
 //   dx_p += w_p A_q^T dH_{u(p)}
-// Launches: prep (A^T, B^T) -> [contract h_p unless the forward's is passed]
-// -> combine (h_u, transposed per key) -> contract dH per row (stored per row
+// Launches: prep (A^T, B^T) -> h_u transposed per key (bf16: gathered from the
+// forward's dense rows, or the contraction with its row sums; fp32: [contract
+// h_p unless the forward's is passed] -> combine) -> contract dH per row (stored per row
 // and, times each pair's weight, per pair position) -> expand dx over the
 // slots of every row -> weight gradients (dB over rows, dA over pairs).
 #include "ace_device.hpp"
@@ -90,6 +96,32 @@ __global__ __launch_bounds__(kThreads) void restride_b_kernel(const T* B, T* Bd,
   Bd[i] = B[(size_t)d_out * roff + (size_t)n * r_q + (K - roff)];
 }
 
+// Ht[roff_q + r][u - offsets[q]] = Hd[t_u][roff_q + r]: the rows' h from the
+// forward's dense per-token rows.  A block takes 64 rows; lane l of wave w
+// handles row 64 b + l and the rank chunks w, w + 4, ... (eight ranks each),
+// so a wave's stores cover 64 consecutive columns.
+__global__ __launch_bounds__(kThreads) void gather_h_kernel(const __bf16* Hd, const int32_t* offsets,
+                                                            const int32_t* row_token, __bf16* Ht,
+                                                            long ldh, KeyTable keys) {
+  __shared__ int seg[kMaxKeys + 1];
+  for (int i = threadIdx.x; i <= keys.n_keys; i += kThreads) seg[i] = offsets[i];
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int u = blockIdx.x * 64 + lane;
+  if (u >= seg[keys.n_keys]) return;
+  const int q = upper_index(seg, keys.n_keys, u);
+  const int r_q = keys.rank[q], roff = keys.roff[q];
+  const __bf16* src = Hd + (size_t)row_token[u] * keys.R + roff;
+  const long col = u - seg[q];
+  const bool vec = ((roff | keys.R | r_q) & 7) == 0;
+  for (int r0 = 8 * wave; r0 < r_q; r0 += 32) {
+    const bf16x8 v = load_frag<__bf16>(src + r0, r_q - r0, vec);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (r0 + e < r_q) Ht[(size_t)(roff + r0 + e) * ldh + col] = v[e];
+  }
+}
+
 // h_p = s_q A_q x_p for every routed pair, row-major per pair position.
 ContractArgs pair_h_args(const Problem& p, void* hp, int rpad) {
   ContractArgs c{};
@@ -109,6 +141,25 @@ ContractArgs pair_h_args(const Problem& p, void* hp, int rpad) {
   c.rpad = rpad;
   c.keys = p.keys;
   return c;
+}
+
+// Whether the contraction sums h per row itself (it finds a tile's rows
+// through pair_row, which a routing built by hand may leave out: then h_p and
+// the combine, as for fp32).
+bool sums_rows(const Problem& p) { return p.dtype == ACE_BF16 && p.rt->pair_row; }
+
+// bf16: the same, summed per row with the pair weights (h_u), into dense
+// per-token rows Hd and/or per key into Ht (either may be null).
+hipError_t launch_row_h(const Problem& p, void* Hd, void* Ht, long ldh, int rpad, hipStream_t stream) {
+  ContractArgs c = pair_h_args(p, nullptr, rpad);
+  c.row_sum = 1;
+  c.pair_row = p.rt->pair_row;
+  c.pair_w = p.pair_w;
+  c.out_dense = Hd;
+  c.kslots = 1;
+  c.out_t = Ht;
+  c.ldh = ldh;
+  return launch_contract(p.dtype, c, p.r_max, (long)p.T * p.k, stream);
 }
 
 }  // namespace
@@ -146,9 +197,13 @@ hipError_t launch_fwd_combined(const Problem& p, void* y, void* ws, hipStream_t 
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  e = launch_contract(p.dtype, pair_h_args(p, base + L.hp, rpad), p.r_max, P, stream);
-  if (e != hipSuccess) return e;
-  e = launch_combine(p, base + L.hp, rpad, nullptr, 0, base + L.Hd, stream);
+  if (sums_rows(p)) {
+    e = launch_row_h(p, base + L.Hd, nullptr, 0, rpad, stream);
+  } else {
+    e = launch_contract(p.dtype, pair_h_args(p, base + L.hp, rpad), p.r_max, P, stream);
+    if (e != hipSuccess) return e;
+    e = launch_combine(p, base + L.hp, rpad, nullptr, 0, base + L.Hd, stream);
+  }
   if (e != hipSuccess) return e;
   DxArgs d{};
   d.dHf = base + L.Hd;
@@ -172,14 +227,28 @@ hipError_t launch_bwd_combined(const Problem& p, const void* dy, void* dx, float
   const long ldh = (long)((((size_t)P) + 7) & ~(size_t)7);
   hipError_t e = launch_prep(p, base + L.At, base + L.Bt, nullptr, 0, stream);
   if (e != hipSuccess) return e;
-  // h per pair position: the forward's (its workspace starts with it) or recomputed
-  const void* hp = p.h_fwd;
-  if (!hp) {
-    hp = base + L.hp;
-    e = launch_contract(p.dtype, pair_h_args(p, base + L.hp, rpad), p.r_max, P, stream);
-    if (e != hipSuccess) return e;
+  if (sums_rows(p)) {
+    if (p.h_fwd) {   // the dense rows in the forward's workspace
+      const FwdLayout F = fwd_layout(p.T, p.k, p.d_out, p.keys.n_keys, p.r_max, es);
+      if (P > 0) {
+        gather_h_kernel<<<(int)((P + 63) / 64), kThreads, 0, stream>>>(
+            reinterpret_cast<const __bf16*>(static_cast<const char*>(p.h_fwd) + F.Hd), p.rt->offsets,
+            p.rt->row_token, reinterpret_cast<__bf16*>(base + L.Ht), ldh, p.keys);
+        e = hipGetLastError();
+      }
+    } else {
+      e = launch_row_h(p, nullptr, base + L.Ht, ldh, rpad, stream);
+    }
+  } else {
+    // h per pair position: the forward's (its workspace starts with it) or recomputed
+    const void* hp = p.h_fwd;
+    if (!hp) {
+      hp = base + L.hp;
+      e = launch_contract(p.dtype, pair_h_args(p, base + L.hp, rpad), p.r_max, P, stream);
+      if (e != hipSuccess) return e;
+    }
+    e = launch_combine(p, hp, rpad, base + L.Ht, ldh, nullptr, stream);
   }
-  e = launch_combine(p, hp, rpad, base + L.Ht, ldh, nullptr, stream);
   if (e != hipSuccess) return e;
   // dH_u = s B^T dOut[t_u], per row (for dx) and times w_p per pair position (for dA)
   ContractArgs c{};
