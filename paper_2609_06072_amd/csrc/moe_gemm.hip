@@ -415,6 +415,36 @@ __global__ __launch_bounds__(Large::THREADS, 1) void moe_gemm_large_kernel(MoeAr
     const int uc = min(u, hi - 1);
     return a.row_token[uc] * a.k + (__builtin_ctz(a.row_slots[uc] | 0x80000000u) & 31);
   };
+  // ---- the adapter's first two K-blocks (h rows of the pairs, B_q rows) into
+  // registers ahead of the copies: loads return in order, so behind them each
+  // step of the chain pair -> h row -> h would wait for copies from HBM
+  F x0[4], x1a[4], x1b[4], wa[16], wb[16];   // x: K-block 0 and 1 of a half, W: [nb + 8 kh]
+  const int q = a.H ? a.key_of[e] : 0;
+  const int r_q = a.H ? a.keys.rank[q] : 0;
+  const __bf16* Bq = static_cast<const __bf16*>(a.B) + (a.H ? (size_t)d_out * a.keys.roff[q] : 0);
+  const __bf16* Hm = static_cast<const __bf16*>(a.H);
+  const bool bvec = (r_q & 7) == 0;
+  int hrow[8];
+  if (r_q > 0) {
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) {
+      const int u = u0 + 128 * wy + 16 * mb + c16;
+      const int hr = a.h_row[pair_of(u)];   // (rows past the segment: its last row's)
+      hrow[mb] = u < hi ? hr : -1;
+    }
+  }
+  auto adapter_load = [&](int kb, F (&f)[16]) {   // B rows, then h rows
+    const int rho = kb * 32 + 8 * g;
+#pragma unroll
+    for (int nb = 0; nb < 8; ++nb) {
+      const int n = min(n0 + 128 * wx + 16 * nb + c16, d_out - 1);
+      f[nb] = load_frag<__bf16>(Bq + (size_t)n * r_q + rho, r_q - rho, bvec);
+    }
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb)
+      f[8 + mb] = hrow[mb] >= 0 ? Tr<__bf16>::load(Hm + (size_t)hrow[mb] * a.rpad + rho) : Tr<__bf16>::zero();
+  };
+
   // ---- copies: waves 0 and 1 copy the x rows of waves (wy = 0, 1), waves 2
   // and 3 the W rows of (wx = 0, 1): of a slot the eight 8-row copies of their
   // 64 rows, lane l the chunk at position l & 7 of row l >> 3.  Rows are byte
@@ -458,6 +488,8 @@ __global__ __launch_bounds__(Large::THREADS, 1) void moe_gemm_large_kernel(MoeAr
     cslot += C::SLOT;
     if (cslot >= cbase + C::SLOTS * C::SLOT) cslot = cbase;
   };
+  if (r_q > 0) adapter_load(0, wa);
+  if (r_q > 32) adapter_load(1, wb);
 #pragma unroll
   for (int v = -2; v < 2; ++v) {
     begin_copies(v);
@@ -471,36 +503,18 @@ __global__ __launch_bounds__(Large::THREADS, 1) void moe_gemm_large_kernel(MoeAr
   for (int nb = 0; nb < 8; ++nb)
 #pragma unroll
     for (int mb = 0; mb < 8; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  F x0[4], x1a[4], x1b[4], wa[16], wb[16];   // x: K-block 0 and 1 of a half, W: [nb + 8 kh]
-  // ---- adapter K-blocks: acc[n][m] += sum_rho B_q[n][rho] h_m[rho], from registers
-  if (a.H) {
-    const int q = a.key_of[e];
-    const int r_q = a.keys.rank[q];
-    const __bf16* Bq = static_cast<const __bf16*>(a.B) + (size_t)d_out * a.keys.roff[q];
-    const __bf16* Hm = static_cast<const __bf16*>(a.H);
-    const bool bvec = (r_q & 7) == 0;
-    int hrow[8];
+  // adapter K-blocks: acc[n][m] += sum_rho B_q[n][rho] h_m[rho]
+  auto adapter_mma = [&](const F (&f)[16]) {
 #pragma unroll
-    for (int mb = 0; mb < 8; ++mb) {
-      const int u = u0 + 128 * wy + 16 * mb + c16;
-      hrow[mb] = u < hi ? a.h_row[pair_of(u)] : -1;
-    }
-    for (int kb = 0; kb * 32 < r_q; ++kb) {
-      const int rho = kb * 32 + 8 * g;
+    for (int nb = 0; nb < 8; ++nb)
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb) {
-        const int n = min(n0 + 128 * wx + 16 * nb + c16, d_out - 1);
-        wa[nb] = load_frag<__bf16>(Bq + (size_t)n * r_q + rho, r_q - rho, bvec);
-      }
-#pragma unroll
-      for (int mb = 0; mb < 8; ++mb)
-        wa[8 + mb] = hrow[mb] >= 0 ? Tr<__bf16>::load(Hm + (size_t)hrow[mb] * a.rpad + rho) : Tr<__bf16>::zero();
-#pragma unroll
-      for (int nb = 0; nb < 8; ++nb)
-#pragma unroll
-        for (int mb = 0; mb < 8; ++mb) mfma_acc(acc[nb][mb], wa[nb], wa[8 + mb]);
-    }
+      for (int mb = 0; mb < 8; ++mb) mfma_acc(acc[nb][mb], f[nb], f[8 + mb]);
+  };
+  if (r_q > 0) adapter_mma(wa);
+  if (r_q > 32) adapter_mma(wb);
+  for (int kb = 2; kb * 32 < r_q; ++kb) {
+    adapter_load(kb, wa);
+    adapter_mma(wa);
   }
 
   // ---- main loop over d_in.  Fragment rows 64 wy + 16 mb + c16 of an x unit
