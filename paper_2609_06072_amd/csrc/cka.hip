@@ -13,7 +13,7 @@
 //
 // Launches (all deterministic):
 //   project -- Pt = A X^T, [R][ldp] fp32: an MFMA GEMM over K = d_in,
-//              operands copied global -> LDS directly; bf16 tiles of 64 to
+//              operands copied global -> LDS directly; bf16 tiles of 32 to
 //              128 probe rows x 256 adapter rows, fp32 64 x 256
 //   mean    -- the probe mean of every row of Pt; bf16 inputs: also the
 //              centred rows split as v = hi + lo (both bf16, |lo| <= 2^-9 |v|)
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kPThreads) void cka_project_kernel(CkaArgs a) {
 // bounds it is the copies' latency (A's rows come from the L2, X's from HBM):
 // a stage's slot takes the copies of the third stage after it as soon as its
 // second K-block's fragments are in registers, so that two to three stages
-// (86 to 144 KB per CU) are in flight against one 40 KB stage per block
+// (74 to 144 KB per CU) are in flight against one 40 KB stage per block
 // before.  PN comes in steps of 16 rows (launch_project): as many blocks as
 // CUs, not half as many again.  OLMoE-like, 10,000 probe rows:
 // 42 -> 32 us (the same tiles with every read and copy of a stage ahead of
@@ -316,8 +316,8 @@ __global__ __launch_bounds__(256, 1) void cka_project_wide_kernel(CkaArgs a) {
     ach[i] = 8 * (cpos ^ cka_sw(r));
   }
   const uint32_t sbase = lds_addr(sm);
-  // copy i of stage st (chunks past d_in repeat the row's last one, masked in
-  // x; stages past the last one repeat it into slots that nothing reads)
+  // copy i of stage st (chunks past d_in repeat the row's last one, masked
+  // before the matrix work; stages past the last one repeat it into slots that nothing reads)
   auto copy = [&](int st, int i) {
     const uint32_t buf = sbase + (st % NBUF) * STAGE;
     const int k0 = min(st, nst - 1) * KS;
@@ -340,17 +340,20 @@ __global__ __launch_bounds__(256, 1) void cka_project_wide_kernel(CkaArgs a) {
   // K-block kb of stage st in (xc, ac): groups of four matrix instructions,
   // between them the reads of the next K-block (sn, kn) and, with COPY, the
   // copies of stage st + NBUF (one wave per SIMD: nothing else hides them)
-  auto kblock = [&](auto copy_c, int st, int kb, F (&xc)[JN], const F (&ac)[4], int sn, int kn,
+  auto kblock = [&](auto copy_c, int st, int kb, F (&xc)[JN], F (&ac)[4], int sn, int kn,
                     F (&xn)[JN], F (&an)[4]) {
     constexpr bool COPY = decltype(copy_c)::value;
-    constexpr int CP = (XC + AC + JN - 1) / JN;
+    constexpr int CP = (XC + AC + JN - 1) / JN, AR = (4 + JN - 1) / JN;   // per group
     if (RAGGED && st * KS + 32 * kb + 8 * g >= d_in) {
 #pragma unroll
       for (int j = 0; j < JN; ++j) xc[j] = Tr<__bf16>::zero();
+#pragma unroll
+      for (int j = 0; j < 4; ++j) ac[j] = Tr<__bf16>::zero();
     }
 #pragma unroll
     for (int jn = 0; jn < JN; ++jn) {
-      if (jn < 4) an[jn] = frag(sn, kn, PN + 64 * wave + 16 * jn);
+#pragma unroll
+      for (int j = jn * AR; j < min((jn + 1) * AR, 4); ++j) an[j] = frag(sn, kn, PN + 64 * wave + 16 * j);
       xn[jn] = frag(sn, kn, 16 * jn);
       if constexpr (COPY) {
 #pragma unroll
@@ -897,13 +900,15 @@ void launch_project_wide(const CkaArgs& a, hipStream_t stream) {
   else cka_project_wide_kernel<PN, false><<<grid, 256, 0, stream>>>(a);
 }
 
-// Probe rows per block: of 64, 80, 96, 112 and 128 the size with the least
+// Probe rows per block: of 32, 48, .. 128 the size with the least
 // rounds of blocks times bytes per block (the time of a block is its copies').
+// Against the eight-wave 64 x 256 tiles: 1000 probe rows of 1024 40.4 -> 35.5
+// us a call (38.6 without the sizes below 64), 500 of 4096 85.7 -> 66.8 (75.3).
 void launch_project(const CkaArgs& a, hipStream_t stream) {
   const long cy = (a.R + kPC - 1) / kPC, cus = device_cu_count();
   int best = 0;
   long cost = 0;
-  for (int pn = 64; pn <= 128; pn += 16) {
+  for (int pn = 32; pn <= 128; pn += 16) {
     const long rounds = (((long)a.N + pn - 1) / pn * cy + cus - 1) / cus;
     const long c = rounds * (pn + kPC);
     if (!best || c < cost) {
@@ -912,6 +917,8 @@ void launch_project(const CkaArgs& a, hipStream_t stream) {
     }
   }
   switch (best) {
+    case 32: return launch_project_wide<32>(a, stream);
+    case 48: return launch_project_wide<48>(a, stream);
     case 64: return launch_project_wide<64>(a, stream);
     case 80: return launch_project_wide<80>(a, stream);
     case 96: return launch_project_wide<96>(a, stream);

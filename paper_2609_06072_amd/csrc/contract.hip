@@ -167,7 +167,8 @@ __global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a
   const int nks = (K + KB - 1) / KB;
   for (int ks = wave; ks < nks; ks += NWV * SU) {
     F sf[SU][NRB], wf[SU][RB];
-    // K-blocks past the end repeat the last chunk of the row, with x zeroed
+    // chunks past the end repeat the row's last one, zeroed below (both
+    // operands: an infinity there must not meet a zero)
 #pragma unroll
     for (int s = 0; s < SU; ++s) {
       const int kof = (ks + NWV * s) * KB + PER * g, kc = min(kof, K - PER);
@@ -185,8 +186,10 @@ __global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a
         for (int ib = 0; ib < NRB; ++ib) {
           if (kof >= K) sf[s][ib] = Tr<T>::zero();
 #pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
+          for (int rb = 0; rb < RB; ++rb) {
+            if (kof >= K) wf[s][rb] = Tr<T>::zero();
             if (rb < nrb) acc[ib][rb] = Tr<T>::mma(wf[s][rb], sf[s][ib], acc[ib][rb]);
+          }
         }
       }
     }
@@ -522,7 +525,13 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP && sizeof(T) == 2 ? 2 : 
       for (int rb = 0; rb < E; ++rb) {
         // weight rows at or past r_q were not copied: their results are zeroed below
         const int wr = rank_of_row<T>(rb, c16);
-        const F wf = *reinterpret_cast<const F*>(&Wb[b][wr * ROWB + ((chunk ^ w_swz<CPR>(wr)) << 4)]);
+        F wf = *reinterpret_cast<const F*>(&Wb[b][wr * ROWB + ((chunk ^ w_swz<CPR>(wr)) << 4)]);
+        if (ragged) {
+          const int nv = K - (kk + PER * g);
+#pragma unroll
+          for (int e = 0; e < PER; ++e)
+            if (e >= nv) wf[e] = (T)0.f;
+        }
         acc[kb % G::NACC][rb] = Tr<T>::mma(wf, sf, acc[kb % G::NACC][rb]);   // D[rank][row]
       }
     };

@@ -449,7 +449,7 @@ __global__ __launch_bounds__(Large::THREADS, 1) void moe_gemm_large_kernel(MoeAr
   // and 3 the W rows of (wx = 0, 1): of a slot the eight 8-row copies of their
   // 64 rows, lane l the chunk at position l & 7 of row l >> 3.  Rows are byte
   // offsets from x or from the tile's first W row; chunks past d_in repeat the
-  // row's last one (masked in the x fragments of the last stage).
+  // row's last one (masked in the fragments of a ragged d_in).
   const int crl = lane >> 3, cpos = lane & 7;
   const bool xwave = wave < 2;
   const char* base = xwave ? reinterpret_cast<const char*>(X)
@@ -688,7 +688,7 @@ __global__ __launch_bounds__(256) void moe_stream_kernel(MoeArgs a) {
   const int nx = min(NRB, max(0, (u_end - u0 + 3) / 4 - wave * NRB));
   const int nst = (d_in + KC - 1) / KC;
   const uint32_t sbase = lds_addr(smem);
-  auto issue = [&](int st) {   // columns past d_in repeat the row's last chunk (masked in x)
+  auto issue = [&](int st) {   // columns past d_in repeat the row's last chunk (masked at the reads)
     const uint32_t buf = sbase + (st % NBUF) * C::STAGE;
     const int k0 = st * KC;
 #pragma unroll
@@ -715,11 +715,13 @@ __global__ __launch_bounds__(256) void moe_stream_kernel(MoeArgs a) {
   auto kblock = [&](int st, int kb, bool ragged) {
     const char* S = smem + (st % NBUF) * C::STAGE;
     const int chunk = ((kb * 4 + g) ^ c16) << 4;   // rows 16 i + c16
-    const F wf = *reinterpret_cast<const F*>(S + (16 * wave + c16) * ROWB + chunk);
+    F wf = *reinterpret_cast<const F*>(S + (16 * wave + c16) * ROWB + chunk);
+    const bool past = ragged && st * KC + kb * KB + PER * g >= d_in;
+    if (past) wf = Tr<T>::zero();
 #pragma unroll
     for (int ib = 0; ib < NRB; ++ib) {
       F xf = *reinterpret_cast<const F*>(S + C::WBYTES + (16 * ib + c16) * ROWB + chunk);
-      if (ragged && st * KC + kb * KB + PER * g >= d_in) xf = Tr<T>::zero();
+      if (past) xf = Tr<T>::zero();
       acc[ib] = Tr<T>::mma(wf, xf, acc[ib]);   // D[column][row]
     }
   };

@@ -1,0 +1,163 @@
+"""Parity at the sizes where a launch rule changes kernel: the permutation's
+chunk counts, the rank contraction's tile sizes, the expert GEMM's row counts,
+the CKA projection's probe tiles, and the pre-combined path with and without
+pair_row.  Oracle and tolerances as in the other GPU tests: integers bit for
+bit, rel-L2 2e-2 (bf16) and 1e-5 (fp32), CKA entries within 1e-4."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_harness import (TOL, check_all, check_dB_rows, f64, make_case, oracle_bwd, oracle_fwd,
+                         run_gpu, say)
+from oracle import ace_oracle as O
+from oracle import consolidation_oracle as C
+from paper_2609_06072_amd import workloads as W
+from test_gpu_moe import case_and_weights, oracle_y, run_moe
+from test_gpu_parity import _perm_check, _perm_compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    from paper_2609_06072_amd import ace  # noqa: F401  (fails loudly if libace.so is missing)
+
+
+@pytest.mark.parametrize("T,k", [(1, 8), (32, 8), (33, 8), (64, 8), (96, 8), (128, 8), (129, 8),
+                                 (103, 5), (8, 32), (25, 32), (33, 32)])
+def test_permute_chunk_counts(T, k):
+    """One launch for up to four chunks of 256 pairs, two from five; with ids
+    out of range, repeated ids and experts outside every group."""
+    from paper_2609_06072_amd import ace
+    say(f"permute T={T} k={k}")
+    rng = np.random.default_rng(T * 100 + k)
+    E, G = 40, 7
+    ids = rng.integers(0, E, size=(T, k)).astype(np.int32)   # repeats within a token
+    ids[rng.random((T, k)) < 0.05] = E + 3
+    ids[rng.random((T, k)) < 0.05] = -1
+    e2g = rng.integers(0, G + 1, size=E).astype(np.int32)    # G: outside [0, G)
+    for mode in (0, 1, 2):
+        _perm_check(ids, E, e2g, G, mode)
+    g, e = ace.ace_group_expert_permute(torch.from_numpy(ids).cuda(), E, torch.from_numpy(e2g).cuda(), G)
+    _perm_compare(g, ids, E, e2g, G, 0)
+    _perm_compare(e, ids, E, e2g, G, 2)
+
+
+# (tokens, E, k, group size, r): tiles of 16 rows (up to 256 of them); one
+# 64-row tile per block (bf16, up to 256); 32-row tiles (fp32, ranks up to 64);
+# 64-row tiles shared out over the XCDs, fp32 keys of mixed ranks among them
+CONTRACT = [
+    ("bf16", 40, 8, 2, ("consecutive", 4), 5),
+    ("bf16", 1984, 8, 2, ("consecutive", 4), 8),     # the last size of 16-row tiles
+    ("bf16", 1985, 8, 2, ("consecutive", 4), 8),
+    ("bf16", 2500, 8, 2, ("consecutive", 4), 16),
+    ("bf16", 2500, 8, 2, ("consecutive", 4), 24),
+    ("bf16", 2500, 8, 2, ("consecutive", 4), 40),
+    ("f32", 40, 8, 2, ("consecutive", 4), 40),
+    ("f32", 2500, 8, 2, ("consecutive", 4), 3),
+    ("f32", 2500, 16, 2, ("uneven", 0), 8),
+    ("f32", 2500, 16, 2, ("uneven", 0), 16),
+    ("f32", 8200, 16, 2, ("uneven", 0), 16),
+    ("f32", 2500, 8, 2, ("consecutive", 4), 40),
+]
+
+
+@pytest.mark.parametrize("dtype,T,E,k,groups,r_e", CONTRACT)
+@pytest.mark.parametrize("path", ["grouped", "down_expertwise"])
+def test_contraction_tiles(dtype, T, E, k, groups, r_e, path):
+    base = W.CONFIGS["olmoe_bf16"]
+    cfg = base.scaled(dtype=dtype, T=T, E=E, k=k, groups=groups, r_e=r_e, d_model=136, d_ffn=72)
+    say(f"contraction {dtype} T={T} E={E} r={r_e} {groups} {path}")
+    c = make_case(cfg, path, seed=3, with_w=path == "grouped")
+    out = run_gpu(c, reuse_h=True)
+    tol = TOL[dtype]
+    check_all("y", f64(out["y"]), oracle_fwd(c), tol)
+    dx, dA, dB = oracle_bwd(c)
+    check_all("dx", f64(out["dx"]), dx, tol)
+    check_all("dA", f64(out["dA"]), dA, tol)
+    check_dB_rows("dB", f64(out["dB"]), dB, c.ranks, c.d_out, tol)
+
+
+# rows per expert on average (T k / E): the streaming kernel's tiles of 16, 32
+# and 64 rows, the medium tiles, the large ones; d_in of one, two, three and a
+# ragged number of 64-index stages, an odd number of column tiles
+@pytest.mark.parametrize("dtype,T", [("bf16", 9), ("bf16", 32), ("bf16", 33), ("bf16", 128), ("bf16", 129),
+                                     ("bf16", 256), ("bf16", 257), ("bf16", 767), ("bf16", 768),
+                                     ("bf16", 1100), ("f32", 32), ("f32", 33), ("f32", 2048), ("f32", 2049)])
+@pytest.mark.parametrize("d_model,d_ffn,r_e", [(64, 128, 8), (192, 328, 24), (256, 520, 5)])
+def test_expert_rows(dtype, T, d_model, d_ffn, r_e):
+    cfg = W.CONFIGS["mixtral_bf16"].scaled(dtype=dtype, T=T, k=1, E=4, d_model=d_model, d_ffn=d_ffn,
+                                           r_e=r_e, groups=("consecutive", 4))
+    for path in ("grouped", "down_expertwise"):
+        say(f"expert rows {dtype} T={T} {d_model}x{d_ffn} r={r_e} {path}")
+        c, Wt = case_and_weights(cfg, path, seed=12)
+        check_all("y", f64(run_moe(c, Wt)), oracle_y(c, Wt), TOL[dtype])
+
+
+def test_expert_rows_empty_and_dropped():
+    """Large tiles with an expert of no rows, one of a single row and dropped
+    pairs: their y rows stay as they were."""
+    cfg = W.CONFIGS["mixtral_bf16"].scaled(T=1500, k=1, E=4, d_model=136, d_ffn=264, r_e=4,
+                                           groups=("consecutive", 2))
+    c, Wt = case_and_weights(cfg, "grouped", seed=13)
+    ids = np.where(np.arange(cfg.T) % 3 == 0, 0, 3).astype(np.int32)[:, None]
+    ids[7] = 1
+    ids[::50] = -1
+    c.rt.topk_ids[:] = ids
+    y0 = torch.full((cfg.P, c.d_out), 7.0, dtype=c.x.dtype, device="cuda")
+    y = f64(run_moe(c, Wt, y=y0))
+    keep = ids[:, 0] >= 0
+    assert np.all(y[~keep] == 7.0)
+    check_all("y", y[keep], oracle_y(c, Wt)[keep], TOL["bf16"])
+
+
+@pytest.mark.parametrize("N", [8192, 9001, 16384, 16388, 20480, 24001, 28000, 32701])
+@pytest.mark.parametrize("d_in", [64, 136])
+def test_cka_probe_tiles(N, d_in):
+    """Probe tiles of 32 to 128 rows in steps of 16 (one round of 256 blocks
+    each) and rows too long for the mean pass's registers (above 16384)."""
+    from paper_2609_06072_amd import ace
+    cfg = W.CONFIGS["olmoe_bf16"].scaled(d_model=d_in, d_ffn=24, E=5, r_e=4, groups=("consecutive", 3))
+    pa = W.make_probe_adapters(cfg, "gate", N=N, seed=2, device="cuda")
+    say(f"cka N={N} d_in={d_in}")
+    S = f64(ace.ace_pairwise_cka(pa.X, pa.A, pa.B, pa.E, pa.r))
+    ref = C.cka_matrix(f64(pa.X), f64(pa.A), f64(pa.B), pa.E, pa.r)
+    assert np.max(np.abs(S - ref)) <= 1e-4
+
+
+@pytest.mark.parametrize("reuse_h", [False, True])
+@pytest.mark.parametrize("pair_row", [True, False])
+@pytest.mark.parametrize("path,r_e", [("combined", 5), ("combined", 16), ("combined_expertwise", 8)])
+def test_combined_row_sums(path, r_e, pair_row, reuse_h, monkeypatch):
+    """bf16 rows summed in the contraction; a routing without pair_row (which
+    these calls don't ask for) takes the pass of its own."""
+    from paper_2609_06072_amd import ace
+    cfg = W.CONFIGS["olmoe_bf16"].scaled(T=333, k=6, E=16, d_model=136, d_ffn=72, r_e=r_e)
+    c = make_case(cfg, path, seed=5, with_w=True)
+    if not pair_row:
+        permute = ace.ace_group_permute
+
+        def without(*a, **kw):
+            rt = permute(*a, **kw)
+            rt.c.pair_row = None
+            return rt
+        monkeypatch.setattr(ace, "ace_group_permute", without)
+    say(f"{path} r={r_e} pair_row={pair_row} reuse_h={reuse_h}")
+    out = run_gpu(c, reuse_h=reuse_h)
+    tol = TOL["bf16"]
+    check_all("y", f64(out["y"]), oracle_fwd(c), tol)
+    dx, dA, dB = oracle_bwd(c)
+    check_all("dx", f64(out["dx"]), dx, tol)
+    check_all("dA", f64(out["dA"]), dA, tol)
+    check_dB_rows("dB", f64(out["dB"]), dB, c.ranks, c.d_out, tol)
+
+
+def test_rank_lists_by_value():
+    """A rank list changed in place between calls is read anew."""
+    cfg = W.CONFIGS["olmoe_bf16"].scaled(T=50, E=4, k=2, groups=("consecutive", 2), d_model=64, d_ffn=64)
+    c = make_case(cfg, "grouped", seed=6)
+    for ranks in ([16, 16], [8, 24], [24, 8]):
+        c.ranks[:] = ranks
+        check_all(f"y {ranks}", f64(run_gpu(c, bwd=False)["y"]), oracle_fwd(c), TOL["bf16"])
