@@ -102,8 +102,8 @@ __device__ inline void contract_store(const ContractArgs& a, int q, int lo, int 
 // ------------------------------------------------------------- small batches
 //
 // Few rows (decode batches): latency bounds a tile, not bytes.  A block of 16
-// waves takes a tile of 16 rows; the waves split the contraction (wave w takes
-// K-blocks w, w + 16, ...), and each loads its fragments straight from global
+// waves (8 above 128 ranks) takes a tile of 16 rows; the waves split the contraction (wave w takes
+// every NWV-th K-block), and each loads its fragments straight from global
 // memory, up to SU K-blocks in flight, so that a contraction of 2048 is one or
 // two round trips; the partial sums meet in LDS in wave order.  OLMoE-like,
 // 32 tokens, d_in 2048: 12.9 -> 9.4 us a call; fp32, 256 tokens,
@@ -595,7 +595,8 @@ hipError_t launch_contract_rb(const ContractArgs& a, long P, hipStream_t stream)
   using G = CDma<T, RB, NWV, false>;
   const long n16 = P > 0 ? (P + 15) / 16 + a.keys.n_keys : 0;   // tiles of 16 rows, at most
   if (n16 > 0 && n16 <= kSmallTiles && !a.row_sum) {
-    contract_small_kernel<T, RB, 1, 16><<<(int)n16, 64 * 16, 0, stream>>>(a);
+    constexpr int W = RB <= 8 ? 16 : 8;   // waves (at 16 the registers of 256 ranks spill)
+    contract_small_kernel<T, RB, 1, W><<<(int)n16, 64 * W, 0, stream>>>(a);
     return hipGetLastError();
   }
   // fp32 at ranks up to 64, whose matrix work fills a tile: tiles of 32 rows
