@@ -205,8 +205,9 @@ ace_status ace_group_expert_permute(const int32_t* topk_ids, int32_t T, int32_t 
  *               accumulated (+=).
  *   ws          device scratch of at least
  *               ace_workspace_bytes(ACE_OP_FWD, T, k, d_in, d_out, G, max r_g)
- *               (it holds h = (alpha/r_g) A_g x per row, per routed pair for
- *               ACE_INPUT_COMBINED); no initialisation.
+ *               (it holds h = (alpha/r_g) A_g x per row; for
+ *               ACE_INPUT_COMBINED per routed pair or summed in dense
+ *               per-token rows); no initialisation.
  * Two launches: the shrink h once per row of the permutation, then the
  * expand B_g h added into every slot the row serves.  ACE_INPUT_COMBINED:
  * h per routed pair, its weighted sum per row into dense per-token rows

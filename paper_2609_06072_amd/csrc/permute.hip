@@ -43,8 +43,9 @@ constexpr int kWordsPerKey = kPairsPerBlock / 64;
 // the scatter folds itself: 32 KiB of LDS as 16-bit counts.
 constexpr int kFoldCells = 16384;
 
-// Chunks up to which each scatter block recounts all of them: a chunk costs a
-// block about 1.2 us, the launch that it saves about 5 us.
+// Chunks up to which each scatter block recounts all of them: one launch of
+// 5.6, 7.3, 8.8 and 10.3 us for one to four chunks (both routings of 32 to 128
+// tokens, top 8 of 64) against 14 us for the two, at any of these sizes.
 constexpr int kRecountBlocks = 4;
 
 struct PermPass {
