@@ -129,7 +129,8 @@ hipError_t launch_moe_gemm(int dtype, const MoeArgs& a, long P, hipStream_t stre
 //         multiple inside a 256-byte padded region).
 //   combine: h_u = sum over the pairs of row u of w_p hp[pos] (hp row-major
 //         [P][rpad] per pair position), written to Ht [R][ldh] (column
-//         u - offsets[q]) and/or Hd [T][R] (dense per token); either may be null.
+//         u - offsets[q]) or to Hd [T][R] (dense per token, summed over the rows
+//         of a token and key where a row is a single pair); the other is null.
 hipError_t launch_prep(const Problem& p, void* At, void* Bt, void* zero, long zero_bytes,
                        hipStream_t stream);
 hipError_t launch_combine(const Problem& p, const void* hp, int rpad, void* Ht, long ldh,

@@ -90,6 +90,9 @@ WsLayout ws_layout(int T, int k, int d_in, int d_out, int n_keys, int R, int r_m
 // [r][u - offsets[q]] for the weight gradient and/or as dense per-token rows
 // for the dx GEMM (either output may be null).  The pre-combined mode uses
 // the same sum for h_u = sum_i w_{p_i} h_{p_i}.
+// With token_rows (one row per pair: a token may have several rows of a key,
+// next to each other) the dense rows hold the sum over all of them, stored by
+// the first one (dHt null).
 struct CombineArgs {
   const int32_t* offsets;
   const int32_t* row_token;
@@ -101,6 +104,7 @@ struct CombineArgs {
   void* dHt;
   long ldh;
   void* dHf;
+  int32_t token_rows;
   KeyTable keys;
 };
 
@@ -124,7 +128,12 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(CombineArgs a) {
   const int r_q = a.keys.rank[q], roff = a.keys.roff[q], R = a.keys.R;
   const long col = u - seg[q];
   const int tok = a.row_token[u];
-  const int p0 = a.ppos[u], p1 = a.ppos[u + 1];
+  int ue = u + 1;   // end of the rows summed
+  if (a.token_rows) {
+    if (u > seg[q] && a.row_token[u - 1] == tok) return;
+    while (ue < seg[q + 1] && a.row_token[ue] == tok) ++ue;
+  }
+  const int p0 = a.ppos[u], p1 = a.ppos[ue];
   const int pb = min(p0 + 1, p1 - 1);
   float w0 = 1.f, w1 = p1 - p0 > 1 ? 1.f : 0.f;
   if (a.pair_w) {
@@ -366,6 +375,7 @@ hipError_t launch_combine_t(const Problem& p, const void* hp, int rpad, void* Ht
   cb.dHt = Ht;
   cb.ldh = ldh;
   cb.dHf = Hd;
+  cb.token_rows = Hd && p.rt->mode == ACE_ROWS_GROUP_PAIRS;
   cb.keys = p.keys;
   const long P = (long)p.T * p.k;
   const int blocks = (int)((P + 63) / 64);

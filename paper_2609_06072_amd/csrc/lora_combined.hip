@@ -9,7 +9,8 @@
 // h_u = s_q A_q z_u as sum_p w_p (s_q A_q x_p):
 //
 // Forward (h stays in the workspace for the backward: the dense h rows for
-// bf16, h_p per pair position for fp32):
+// bf16, h_p per pair position for fp32 and for group-keyed rows of single
+// pairs, which the combine sums per (token, key)):
 //   prep      -- B^T rows [R][d_out] (matrix-core GEMM operand) or B
 //                re-strided to [d_out][R] (register GEMM); zero the dense
 //                per-token h rows.
@@ -145,8 +146,12 @@ ContractArgs pair_h_args(const Problem& p, void* hp, int rpad) {
 
 // Whether the contraction sums h per row itself (it finds a tile's rows
 // through pair_row, which a routing built by hand may leave out: then h_p and
-// the combine, as for fp32).
-bool sums_rows(const Problem& p) { return p.dtype == ACE_BF16 && p.rt->pair_row; }
+// the combine, as for fp32).  Rows that are single pairs (group-keyed) may
+// share a token and a key: their h can't be read back from one dense row, so
+// they take h_p as well.
+bool sums_rows(const Problem& p) {
+  return p.dtype == ACE_BF16 && p.rt->mode != ACE_ROWS_GROUP_PAIRS && p.rt->pair_row;
+}
 
 // bf16: the same, summed per row with the pair weights (h_u), into dense
 // per-token rows Hd and/or per key into Ht (either may be null).

@@ -25,6 +25,7 @@ PATHS = {
     # down projection with the output combined per token (per-pair input)
     "combined": (W.ROWS_GROUP_DEDUP, W.INPUT_COMBINED, "group"),
     "combined_expertwise": (W.ROWS_EXPERT, W.INPUT_COMBINED, "expert"),
+    "combined_pairs": (W.ROWS_GROUP_PAIRS, W.INPUT_COMBINED, "group"),
 }
 WEIGHTED = ("grouped", "pairs_per_pair", "combined", "combined_expertwise")
 

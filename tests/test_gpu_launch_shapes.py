@@ -154,6 +154,25 @@ def test_combined_row_sums(path, r_e, pair_row, reuse_h, monkeypatch):
     check_dB_rows("dB", f64(out["dB"]), dB, c.ranks, c.d_out, tol)
 
 
+@pytest.mark.parametrize("reuse_h", [False, True])
+@pytest.mark.parametrize("with_w", [False, True])
+@pytest.mark.parametrize("dtype,T", [("bf16", 57), ("bf16", 900), ("f32", 57), ("f32", 900)])
+def test_combined_single_pair_rows(dtype, T, with_w, reuse_h):
+    """Pre-combined output over group-keyed rows of single pairs: a token has
+    several rows of a group, whose h add up in its dense row while dB keeps
+    each row's own."""
+    cfg = W.CONFIGS["olmoe_bf16"].scaled(dtype=dtype, T=T, k=6, E=16, d_model=136, d_ffn=72, r_e=8)
+    c = make_case(cfg, "combined_pairs", seed=8, with_w=with_w)
+    say(f"combined pairs {dtype} T={T} w={with_w} reuse_h={reuse_h}")
+    out = run_gpu(c, reuse_h=reuse_h)
+    tol = TOL[dtype]
+    check_all("y", f64(out["y"]), oracle_fwd(c), tol)
+    dx, dA, dB = oracle_bwd(c)
+    check_all("dx", f64(out["dx"]), dx, tol)
+    check_all("dA", f64(out["dA"]), dA, tol)
+    check_dB_rows("dB", f64(out["dB"]), dB, c.ranks, c.d_out, tol)
+
+
 def test_rank_lists_by_value():
     """A rank list changed in place between calls is read anew."""
     cfg = W.CONFIGS["olmoe_bf16"].scaled(T=50, E=4, k=2, groups=("consecutive", 2), d_model=64, d_ffn=64)
