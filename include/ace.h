@@ -206,11 +206,12 @@ ace_status ace_group_expert_permute(const int32_t* topk_ids, int32_t T, int32_t 
  *   ws          device scratch of at least
  *               ace_workspace_bytes(ACE_OP_FWD, T, k, d_in, d_out, G, max r_g)
  *               (it holds h = (alpha/r_g) A_g x per row; for
- *               ACE_INPUT_COMBINED per routed pair or summed in dense
- *               per-token rows); no initialisation.
+ *               ACE_INPUT_COMBINED summed in dense per-token rows (bf16), or per
+ *               routed pair (fp32, and ACE_ROWS_GROUP_PAIRS rows)); no
+ *               initialisation.
  * Two launches: the shrink h once per row of the permutation, then the
  * expand B_g h added into every slot the row serves.  ACE_INPUT_COMBINED:
- * h per routed pair, its weighted sum per row into dense per-token rows
+ * h per routed pair, its weighted sum per row in dense per-token rows
  * [T, R], and y += those rows times B^T (a GEMM over K = R).
  */
 ace_status ace_grouped_lora_fwd(ace_dtype dtype, ace_input_mode input_mode, int32_t T,

@@ -44,8 +44,9 @@ struct FwdLayout {
   size_t hp, Hd, Bm, total;
 };
 
-// hp [P][rpad] first (a backward reads it from there), dense h rows [T][R],
-// the B operand of the GEMM ([R][d_out] or [d_out][R]); R <= n_keys * r_max.
+// hp [P][rpad] first, dense h rows [T][R] (a backward reads one or the other,
+// see dense_h; the place of hp does not depend on which), the B operand of the
+// GEMM ([R][d_out] or [d_out][R]); R <= n_keys * r_max.
 FwdLayout fwd_layout(int T, int k, int d_out, int n_keys, int r_max, size_t es) {
   const size_t P = (size_t)T * k;
   const size_t Rb = (size_t)n_keys * r_max;
@@ -144,14 +145,16 @@ ContractArgs pair_h_args(const Problem& p, void* hp, int rpad) {
   return c;
 }
 
+// Where the forward leaves h for the backward: in the dense per-token rows
+// (bf16), or as h_p per pair position: fp32, and rows that are single pairs
+// (group-keyed), which may share a token and a key, so that their h can't be
+// read back from one dense row.  Type and row mode alone decide it.
+bool dense_h(const Problem& p) { return p.dtype == ACE_BF16 && p.rt->mode != ACE_ROWS_GROUP_PAIRS; }
+
 // Whether the contraction sums h per row itself (it finds a tile's rows
 // through pair_row, which a routing built by hand may leave out: then h_p and
-// the combine, as for fp32).  Rows that are single pairs (group-keyed) may
-// share a token and a key: their h can't be read back from one dense row, so
-// they take h_p as well.
-bool sums_rows(const Problem& p) {
-  return p.dtype == ACE_BF16 && p.rt->mode != ACE_ROWS_GROUP_PAIRS && p.rt->pair_row;
-}
+// the combine, as for fp32).
+bool sums_rows(const Problem& p) { return dense_h(p) && p.rt->pair_row; }
 
 // bf16: the same, summed per row with the pair weights (h_u), into dense
 // per-token rows Hd and/or per key into Ht (either may be null).
@@ -232,18 +235,16 @@ hipError_t launch_bwd_combined(const Problem& p, const void* dy, void* dx, float
   const long ldh = (long)((((size_t)P) + 7) & ~(size_t)7);
   hipError_t e = launch_prep(p, base + L.At, base + L.Bt, nullptr, 0, stream);
   if (e != hipSuccess) return e;
-  if (sums_rows(p)) {
-    if (p.h_fwd) {   // the dense rows in the forward's workspace
-      const FwdLayout F = fwd_layout(p.T, p.k, p.d_out, p.keys.n_keys, p.r_max, es);
-      if (P > 0) {
-        gather_h_kernel<<<(int)((P + 63) / 64), kThreads, 0, stream>>>(
-            reinterpret_cast<const __bf16*>(static_cast<const char*>(p.h_fwd) + F.Hd), p.rt->offsets,
-            p.rt->row_token, reinterpret_cast<__bf16*>(base + L.Ht), ldh, p.keys);
-        e = hipGetLastError();
-      }
-    } else {
-      e = launch_row_h(p, nullptr, base + L.Ht, ldh, rpad, stream);
+  if (p.h_fwd && dense_h(p)) {   // the dense rows in the forward's workspace
+    const FwdLayout F = fwd_layout(p.T, p.k, p.d_out, p.keys.n_keys, p.r_max, es);
+    if (P > 0) {
+      gather_h_kernel<<<(int)((P + 63) / 64), kThreads, 0, stream>>>(
+          reinterpret_cast<const __bf16*>(static_cast<const char*>(p.h_fwd) + F.Hd), p.rt->offsets,
+          p.rt->row_token, reinterpret_cast<__bf16*>(base + L.Ht), ldh, p.keys);
+      e = hipGetLastError();
     }
+  } else if (sums_rows(p)) {
+    e = launch_row_h(p, nullptr, base + L.Ht, ldh, rpad, stream);
   } else {
     // h per pair position: the forward's (its workspace starts with it) or recomputed
     const void* hp = p.h_fwd;

@@ -154,6 +154,36 @@ def test_combined_row_sums(path, r_e, pair_row, reuse_h, monkeypatch):
     check_dB_rows("dB", f64(out["dB"]), dB, c.ranks, c.d_out, tol)
 
 
+@pytest.mark.parametrize("path", ["combined", "combined_pairs"])
+@pytest.mark.parametrize("fwd_pair_row,bwd_pair_row", [(True, False), (False, True)])
+def test_combined_h_place(path, fwd_pair_row, bwd_pair_row):
+    """Where the backward finds the forward's h (bf16) depends on the type and
+    the row mode, not on whether either call's routing has pair_row."""
+    from paper_2609_06072_amd import ace
+    cfg = W.CONFIGS["olmoe_bf16"].scaled(T=333, k=6, E=16, d_model=136, d_ffn=72, r_e=8)
+    c = make_case(cfg, path, seed=9, with_w=True)
+    say(f"{path} pair_row fwd={fwd_pair_row} bwd={bwd_pair_row}")
+    rt = ace.ace_group_permute(torch.from_numpy(c.rt.topk_ids).cuda(), cfg.E,
+                               torch.from_numpy(c.rt.expert_to_group).cuda(), c.rt.G, c.mode)
+    pair_row = rt.c.pair_row
+    need = ace.ace_workspace_bytes(ace.ACE_OP_FWD, cfg.T, cfg.k, c.d_in, c.d_out, c.n_keys, max(c.ranks))
+    ws = torch.full((need,), 0xff, dtype=torch.uint8, device="cuda")   # NaN where nothing is stored
+    y = torch.zeros(cfg.T, c.d_out, dtype=c.x.dtype, device="cuda")
+    rt.c.pair_row = pair_row if fwd_pair_row else None
+    ace.ace_grouped_lora_fwd(c.x, c.A, c.B, c.ranks, cfg.alpha, rt, y, c.pair_w, c.input_mode, ws)
+    dx, dA = torch.zeros_like(c.x), torch.empty(sum(c.ranks), c.d_in, device="cuda")
+    dB = torch.empty(sum(c.ranks) * c.d_out, device="cuda")
+    rt.c.pair_row = pair_row if bwd_pair_row else None
+    ace.ace_grouped_lora_bwd(c.x, c.A, c.B, c.ranks, cfg.alpha, rt, c.dy, dx, dA, dB, c.pair_w, c.input_mode,
+                             h_fwd=ws)
+    tol = TOL["bf16"]
+    check_all("y", f64(y), oracle_fwd(c), tol)
+    rx, rA, rB = oracle_bwd(c)
+    check_all("dx", f64(dx), rx, tol)
+    check_all("dA", f64(dA), rA, tol)
+    check_dB_rows("dB", f64(dB), rB, c.ranks, c.d_out, tol)
+
+
 @pytest.mark.parametrize("reuse_h", [False, True])
 @pytest.mark.parametrize("with_w", [False, True])
 @pytest.mark.parametrize("dtype,T", [("bf16", 57), ("bf16", 900), ("f32", 57), ("f32", 900)])
