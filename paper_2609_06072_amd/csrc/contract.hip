@@ -350,7 +350,7 @@ __device__ inline void row_sum_store(const ContractArgs& a, int q, const f32x4 (
         if (r0 + e < r_q) dt[(size_t)(roff + r0 + e) * a.ldh + col] = v[e];
     }
     if (df) {
-      if (r0 + 8 <= r_q && ((roff + r0) & 7) == 0) {
+      if (r0 + 8 <= r_q && (((roff + r0) | R) & 7) == 0) {   // 16-byte aligned in every token's row
         Tr<__bf16>::store(df + r0, v);
       } else {
 #pragma unroll

@@ -154,6 +154,25 @@ def test_combined_row_sums(path, r_e, pair_row, reuse_h, monkeypatch):
     check_dB_rows("dB", f64(out["dB"]), dB, c.ranks, c.d_out, tol)
 
 
+@pytest.mark.parametrize("path", ["combined", "combined_expertwise", "grouped"])
+@pytest.mark.parametrize("E,r_e", [(60, 5), (15, 5), (6, 6), (12, 12)])
+def test_row_sums_ragged_rank_total(path, E, r_e):
+    """Dense rows of a total rank that is no multiple of 8 (300, 75, 36): a
+    rank chunk that starts at a multiple of 8 is 16-byte aligned in some
+    tokens' rows only (144: in all of them)."""
+    cfg = W.CONFIGS["olmoe_bf16"].scaled(T=333, k=3, E=E, d_model=136, d_ffn=72, r_e=r_e,
+                                         groups=("consecutive", 4))
+    c = make_case(cfg, path, seed=10, with_w=True)
+    say(f"{path} total rank {sum(c.ranks)}")
+    out = run_gpu(c, reuse_h=True)
+    tol = TOL["bf16"]
+    check_all("y", f64(out["y"]), oracle_fwd(c), tol)
+    dx, dA, dB = oracle_bwd(c)
+    check_all("dx", f64(out["dx"]), dx, tol)
+    check_all("dA", f64(out["dA"]), dA, tol)
+    check_dB_rows("dB", f64(out["dB"]), dB, c.ranks, c.d_out, tol)
+
+
 @pytest.mark.parametrize("path", ["combined", "combined_pairs"])
 @pytest.mark.parametrize("fwd_pair_row,bwd_pair_row", [(True, False), (False, True)])
 def test_combined_h_place(path, fwd_pair_row, bwd_pair_row):
