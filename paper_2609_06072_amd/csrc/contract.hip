@@ -15,8 +15,6 @@
 //   row-major  [U][rpad]      operand of the expand kernel (zero beyond r_q)
 //   per key    [R][ldh]       column u - offsets[q]: operand of the column pass
 //   dense      [T*kslots][R]  per-token rows: operand of the dense dx GEMM
-#include <type_traits>
-
 #include "ace_device.hpp"
 #include "ace_internal.hpp"
 
@@ -101,17 +99,15 @@ __device__ inline void contract_store(const ContractArgs& a, int q, int lo, int 
 
 // ------------------------------------------------------------- small batches
 //
-// Few rows (decode batches): latency bounds a tile, not bytes.  A block of 16
-// waves (8 above 128 ranks) takes a tile of 16 rows; the waves split the contraction (wave w takes
-// every NWV-th K-block), and each loads its fragments straight from global
-// memory, up to SU K-blocks in flight, so that a contraction of 2048 is one or
-// two round trips; the partial sums meet in LDS in wave order.  OLMoE-like,
-// 32 tokens, d_in 2048: 12.9 -> 9.4 us a call; fp32, 256 tokens,
+// Few rows (decode batches): latency bounds a tile, not bytes.  A block of 8
+// or 16 waves takes a tile of 16 rows; the waves split the contraction (wave w
+// takes every NWV-th K-block), and each loads its fragments straight from
+// global memory, up to SU K-blocks in flight, so that a contraction of 2048 is
+// one or two round trips; the partial sums meet in LDS in wave order.
+// OLMoE-like, 32 tokens, d_in 2048: 12.9 -> 9.4 us a call; fp32, 256 tokens,
 // d_in 512 and 1024: 11.5 -> 8.8 and 15.2 -> 7.8 us.
-// tiles (at most) up to which small batches go this way: above, the tiles
-// re-read the weights too often (1000 tokens, 564 tiles: a pass of the three
-// adapters takes 105 us with it, 86 without; 400 tokens, 216 tiles: 67 against 71)
-constexpr long kSmallTiles = 256;
+// fp32, whose matrix work fills a tile, also takes larger batches this way, in
+// tiles of 32 rows up to 128 ranks (launch_contract_f32).
 // NRB row blocks of 16 per tile, NWV waves
 template <int RB, int NRB_, int NWV_>
 struct CSmall {
@@ -121,7 +117,7 @@ struct CSmall {
 };
 
 template <typename T, int RB, int NRB, int NWV>
-__global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a) {
+__global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a, int tile0) {
   using F = typename Tr<T>::frag;
   using G = CSmall<RB, NRB, NWV>;
   constexpr int PER = Tr<T>::PER, KB = Tr<T>::KB, SU = G::SU;
@@ -130,7 +126,7 @@ __global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, g = lane >> 4;
   int q, u0, u_end, lo;
-  if (!locate_tile(a.offsets, n_keys, 16 * NRB, blockIdx.x, &q, &u0, &u_end,
+  if (!locate_tile(a.offsets, n_keys, 16 * NRB, tile0 + blockIdx.x, &q, &u0, &u_end,
                    a.src_mode == kSrcPairList ? a.ppos : nullptr, &lo))
     return;
   q = __builtin_amdgcn_readfirstlane(q);
@@ -232,7 +228,177 @@ __global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a
   }
 }
 
-// ------------------------------------------------------------- larger batches
+// ------------------------------------------------------- fp32, larger batches
+//
+// A block of four waves takes a tile of 64 rows (32 from 65 ranks); the waves
+// split the contraction and keep the next K-blocks' fragments in flight in
+// registers, so the weights are read half as often as by 32-row tiles (the
+// same at 32) and no K-block waits for its loads; the partial sums meet in
+// LDS in a fixed order.  Every sum is four chains of a quarter of the
+// contraction.  Tiles go to the XCDs by token range, as in contract_dma.
+template <int RB>
+struct CReg {
+  static constexpr int NRB = RB <= 4 ? 4 : 2;   // 16-row blocks per tile
+  static constexpr int UNROLL = 2;             // K-blocks per stage
+};
+
+template <int RB>
+__global__ __launch_bounds__(kThreads) void contract_reg_kernel(ContractArgs a) {
+  using T = float;
+  using F = typename Tr<T>::frag;
+  constexpr int PER = Tr<T>::PER, KB = Tr<T>::KB, APF = Tr<T>::APF;
+  constexpr int NRB = CReg<RB>::NRB, U = CReg<RB>::UNROLL;
+  constexpr int BM = 16 * NRB;
+  __shared__ int seg[kMaxKeys + 1];
+  __shared__ int bstart[kMaxKeys + 1];
+  __shared__ int bfirst[kMaxKeys];
+  __shared__ int scan[kThreads];
+  __shared__ f32x4 red[4][NRB][RB][64];
+  const int n_keys = a.keys.n_keys;
+  const int bucket = blockIdx.x % kXcds;
+  build_bucket_table(a.offsets, a.src_mode == kSrcPairList ? a.ppos : nullptr, n_keys, BM, bucket,
+                     seg, bstart, bfirst, scan);
+  const int total = bstart[n_keys];
+  const int stride = gridDim.x / kXcds;  // the grid is a multiple of kXcds
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c16 = lane & 15, g = lane >> 4;
+  const T* S = static_cast<const T*>(a.src);
+  const T* W = static_cast<const T*>(a.W);
+  const int K = a.K, k = a.k;
+  const int nks = (K + KB - 1) / KB, nks_full = K / KB;
+
+  for (int idx = blockIdx.x / kXcds; idx < total; idx += stride) {
+    const int q = upper_index(bstart, n_keys, idx);
+    const int lo = seg[q];
+    const int u0 = lo + (bfirst[q] + idx - bstart[q]) * BM;
+    const int u_end = seg[q + 1];
+    const int r_q = a.keys.rank[q], roff = a.keys.roff[q];
+    const int nmb = (r_q + KB - 1) / KB;
+    const int nrb = nmb * APF;  // rank blocks spanned by rank_of_row for r < r_q
+
+    // Source rows.  Rows past the segment re-read the last row (never
+    // stored); weight rows past r_q re-read row r_q - 1 (zeroed before any
+    // store), so every load is unconditional and a wave keeps all of them in
+    // flight.
+    const T* srow[NRB];
+    int sv[NRB];
+    uint32_t slv[NRB];
+#pragma unroll
+    for (int ib = 0; ib < NRB; ++ib) {  // unconditional loads: one round trip
+      const int uc = min(u0 + 16 * ib + c16, u_end - 1);
+      if (a.src_mode == kSrcPairList) {
+        sv[ib] = a.plist[uc];
+        slv[ib] = 1u;
+      } else {
+        sv[ib] = a.row_token[uc];
+        slv[ib] = a.row_slots[uc];
+      }
+    }
+#pragma unroll
+    for (int ib = 0; ib < NRB; ++ib) {
+      const int j0 = __builtin_ctz(slv[ib] | 0x80000000u) & 31;
+      const int sr = a.src_mode == kSrcPerPair ? sv[ib] * k + j0 : sv[ib];
+      srow[ib] = S + (size_t)sr * K;
+    }
+    const T* wrow[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int r = rank_of_row<T>(rb, c16);
+      wrow[rb] = W + (size_t)(roff + (r < r_q ? r : r_q - 1)) * a.ldw;
+    }
+
+    f32x4 acc[NRB][RB];
+#pragma unroll
+    for (int ib = 0; ib < NRB; ++ib)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) acc[ib][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // Main loop over this wave's full stages (U K-blocks each), register
+    // double-buffered: the next stage's loads are in flight while the
+    // matrix cores work on the current one.
+    struct Stage {
+      F sf[U][NRB];
+      F wf[U][RB];
+    };
+    auto load_stage = [&](int ks0, Stage& st) {
+#pragma unroll
+      for (int s = 0; s < U; ++s) {
+        const int kof = (ks0 + 4 * s) * KB + PER * g;
+#pragma unroll
+        for (int ib = 0; ib < NRB; ++ib) st.sf[s][ib] = Tr<T>::load(srow[ib] + kof);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) st.wf[s][rb] = Tr<T>::load(wrow[rb] + kof);
+      }
+    };
+    auto mma_stage = [&](const Stage& st) {
+#pragma unroll
+      for (int s = 0; s < U; ++s)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+          if (rb < nrb) {
+#pragma unroll
+            for (int ib = 0; ib < NRB; ++ib) acc[ib][rb] = Tr<T>::mma(st.wf[s][rb], st.sf[s][ib], acc[ib][rb]);
+          }
+    };
+    // stages of this wave: ks0 = wave + 4*U*i with ks0 + 4*(U-1) < nks_full
+    const int n_main = nks_full > wave + 4 * (U - 1) ? (nks_full - wave - 4 * (U - 1) + 4 * U - 1) / (4 * U) : 0;
+    {
+      Stage SA, SB;
+      if (n_main > 0) load_stage(wave, SA);
+      int i = 0;
+      for (; i + 1 < n_main; i += 2) {
+        load_stage(wave + 4 * U * (i + 1), SB);
+        mma_stage(SA);
+        if (i + 2 < n_main) load_stage(wave + 4 * U * (i + 2), SA);
+        mma_stage(SB);
+      }
+      if (i < n_main) mma_stage(SA);
+    }
+    int ks0 = wave + 4 * U * n_main;
+    for (; ks0 < nks; ks0 += 4) {  // leftover K-blocks of this wave (masked tail)
+      const int kof = ks0 * KB + PER * g;
+      const int nv = K - kof;
+      const int kc = nv > 0 ? kof : 0;
+      F sf[NRB], wf[RB];
+#pragma unroll
+      for (int ib = 0; ib < NRB; ++ib) sf[ib] = nv > 0 ? load_frag<T>(srow[ib] + kc, nv, true) : Tr<T>::zero();
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) wf[rb] = load_frag<T>(wrow[rb] + kc, nv, true);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+        if (rb < nrb) {
+#pragma unroll
+          for (int ib = 0; ib < NRB; ++ib) acc[ib][rb] = Tr<T>::mma(wf[rb], sf[ib], acc[ib][rb]);
+        }
+    }
+
+    // ---- partial sums meet in LDS; wave w finishes row block w % NRB
+    __syncthreads();
+#pragma unroll
+    for (int ib = 0; ib < NRB; ++ib)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) red[wave][ib][rb][lane] = acc[ib][rb];
+    __syncthreads();
+    const int ib = wave % NRB;
+    if (wave >= NRB) continue;  // the other waves' row blocks are done by waves < NRB
+    const int u = u0 + 16 * ib + c16;
+    if (u0 + 16 * ib >= u_end) continue;  // wave-uniform
+    const bool valid = u < u_end;
+    const float s = a.alpha / (float)r_q;
+    f32x4 h[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      h[rb] = (((red[0][ib][rb][lane] + red[1][ib][rb][lane]) + red[2][ib][rb][lane]) +
+               red[3][ib][rb][lane]) * s;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (rank_of_row<T>(rb, 4 * g + v) >= r_q) h[rb][v] = 0.f;
+    }
+    if (!valid) continue;
+    contract_store<T, RB>(a, q, lo, u, h);
+  }
+}
+
+// ------------------------------------------------------- bf16, larger batches
 //
 // A block takes a tile of 64 rows of one key; wave w owns rows 16w .. 16w+15
 // for every rank over the whole contraction, so no cross-wave reduction is
@@ -253,18 +419,14 @@ __global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a
 // LDS instead of sharing it with other blocks, a block takes one tile, found
 // without barriers.  OLMoE-like, 1000 tokens (188 tiles at most): a pass of
 // the three adapters 96 -> 86 us.
-template <typename T, int RB, int NWV, bool DEEP>
+template <int RB, int NWV, bool DEEP>
 struct CDma {
-  static constexpr bool F32 = sizeof(T) == 4;
   // bytes of a row per stage and stages in LDS: ranks up to 32 take 256-byte
   // stages two deep (three blocks per CU); larger ranks, whose weight rows
-  // double the bytes of a stage, 128-byte stages three deep (bf16).  fp32
-  // keeps 256 bytes (four K-blocks): it sums every fourth K-block apart, so
-  // that its chains of additions stay a quarter of the contraction.
-  static constexpr int ROWB = RB <= 2 || (DEEP && RB == 4) || (F32 && RB <= 8) ? 256 : 128;
-  static constexpr int NBUF = DEEP ? (ROWB == 256 && RB >= 4 ? (RB == 8 ? 3 : 4) : 6) : ROWB == 256 ? 2 : 3;
-  static constexpr int KC = ROWB / (int)sizeof(T);   // contraction indices per stage
-  static constexpr int NACC = F32 ? KC / Tr<T>::KB : 1;
+  // double the bytes of a stage, 128-byte stages three deep
+  static constexpr int ROWB = RB <= 2 || (DEEP && RB == 4) ? 256 : 128;
+  static constexpr int NBUF = DEEP ? (RB == 4 ? 4 : 6) : ROWB == 256 ? 2 : 3;
+  static constexpr int KC = ROWB / 2;            // contraction indices per stage
   static constexpr int THREADS = 64 * NWV;       // NWV waves of 16 tile rows each
   static constexpr int ROWS = 16 * NWV;          // tile rows
   static constexpr int CPR = ROWB / 16;          // 16-byte chunks per row piece
@@ -310,7 +472,7 @@ template <int RB, int NWV, bool DEEP>
 __device__ inline void row_sum_store(const ContractArgs& a, int q, const f32x4 (&acc)[RB], float s,
                                      float pw, int ua, int ub, int p0, int rfirst, int rstart,
                                      int rend, int rtok, float* hp) {
-  constexpr int RPS = CDma<__bf16, RB, NWV, DEEP>::RPS;
+  constexpr int RPS = CDma<RB, NWV, DEEP>::RPS;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c16 = lane & 15, g = lane >> 4;
   const int r_q = a.keys.rank[q], roff = a.keys.roff[q], R = a.keys.R;
@@ -361,9 +523,10 @@ __device__ inline void row_sum_store(const ContractArgs& a, int q, const f32x4 (
   }
 }
 
-template <typename T, int RB, int NWV, bool DEEP>
-__global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP && sizeof(T) == 2 ? 2 : 1) void contract_dma_kernel(ContractArgs a) {
-  using G = CDma<T, RB, NWV, DEEP>;
+template <int RB, int NWV, bool DEEP>
+__global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_dma_kernel(ContractArgs a) {
+  using T = __bf16;
+  using G = CDma<RB, NWV, DEEP>;
   using F = typename Tr<T>::frag;
   constexpr int KC = G::KC, NBUF = G::NBUF, KB = Tr<T>::KB, PER = Tr<T>::PER, ROWB = G::ROWB;
   constexpr int CPR = G::CPR, RPI = G::RPI;
@@ -382,7 +545,7 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP && sizeof(T) == 2 ? 2 : 
   const int n_keys = a.keys.n_keys;
   const int bucket = blockIdx.x % kXcds;
   const int K = a.K, k = a.k;
-  const bool rsum = !G::F32 && a.row_sum != 0;   // implies kSrcPairList
+  const bool rsum = a.row_sum != 0;   // implies kSrcPairList
   const int TS = contract_tile(a.row_sum, k, G::ROWS);
   const int32_t* seg_map = a.src_mode == kSrcPairList ? a.ppos : nullptr;
   int total = 1, stride = 1;
@@ -491,11 +654,9 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP && sizeof(T) == 2 ? 2 : 
     const int per_stage = ns + nw;   // copies per stage of this wave
 
     __syncthreads();  // the previous tile is done with the buffers
-    f32x4 acc[G::NACC][RB];
+    f32x4 acc[RB];
 #pragma unroll
-    for (int x = 0; x < G::NACC; ++x)
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) acc[x][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int rb = 0; rb < RB; ++rb) acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int p = 0; p < NBUF - 1; ++p)
       if (p < nst) issue(p);
@@ -506,10 +667,9 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP && sizeof(T) == 2 ? 2 : 
       __syncthreads();
       if (st + NBUF - 1 < nst) issue(st + NBUF - 1);
     };
-    // K-block kb of stage st for the first E rank blocks; the ragged form
-    // masks the indices past the block's range
-    auto kblock = [&](auto e_c, int st, int kb, bool ragged) {
-      constexpr int E = decltype(e_c)::value;
+    // K-block kb of stage st; the ragged form masks the indices past the
+    // block's range
+    auto kblock = [&](int st, int kb, bool ragged) {
       const int b = st % NBUF;
       const int kk = st * KC + kb * KB;
       const int chunk = kb * 4 + g;
@@ -522,7 +682,7 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP && sizeof(T) == 2 ? 2 : 
           if (e >= nv) sf[e] = (T)0.f;
       }
 #pragma unroll
-      for (int rb = 0; rb < E; ++rb) {
+      for (int rb = 0; rb < RB; ++rb) {
         // weight rows at or past r_q were not copied: their results are zeroed below
         const int wr = rank_of_row<T>(rb, c16);
         F wf = *reinterpret_cast<const F*>(&Wb[b][wr * ROWB + ((chunk ^ w_swz<CPR>(wr)) << 4)]);
@@ -532,46 +692,30 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP && sizeof(T) == 2 ? 2 : 
           for (int e = 0; e < PER; ++e)
             if (e >= nv) wf[e] = (T)0.f;
         }
-        acc[kb % G::NACC][rb] = Tr<T>::mma(wf, sf, acc[kb % G::NACC][rb]);   // D[rank][row]
+        acc[rb] = Tr<T>::mma(wf, sf, acc[rb]);   // D[rank][row]
       }
     };
     // full stages: a loop with no branch around the matrix work (a branch
     // there made the compiler copy the accumulators every stage)
     const int nst_full = K / KC;
-    auto contract_all = [&](auto e_c) {
-      for (int st = 0; st < nst_full; ++st) {
-        begin_stage(st);
+    for (int st = 0; st < nst_full; ++st) {
+      begin_stage(st);
 #pragma unroll
-        for (int kb = 0; kb < KC / KB; ++kb) kblock(e_c, st, kb, false);
-      }
-      if (nst_full < nst) {   // block-uniform: the last, partial stage
-        const int st = nst_full;
-        begin_stage(st);
+      for (int kb = 0; kb < KC / KB; ++kb) kblock(st, kb, false);
+    }
+    if (nst_full < nst) {   // block-uniform: the last, partial stage
+      const int st = nst_full;
+      begin_stage(st);
 #pragma unroll
-        for (int kb = 0; kb < KC / KB; ++kb) {
-          const int kk = st * KC + kb * KB;
-          if (kk < K) kblock(e_c, st, kb, kk + KB > K);
-        }
+      for (int kb = 0; kb < KC / KB; ++kb) {
+        const int kk = st * KC + kb * KB;
+        if (kk < K) kblock(st, kb, kk + KB > K);
       }
-    };
-    // fp32 matrix work is 16 times dearer than bf16's: keys of small rank in
-    // a call of larger ones leave out the rank blocks that they don't have
-    const int nrb = (r_q + 15) / 16;
-    if constexpr (G::F32 && RB >= 4) {
-      if (nrb <= RB / 4) contract_all(std::integral_constant<int, RB / 4>{});
-      else if (nrb <= RB / 2) contract_all(std::integral_constant<int, RB / 2>{});
-      else contract_all(std::integral_constant<int, RB>{});
-    } else {
-      contract_all(std::integral_constant<int, RB>{});
     }
 
     const float s = a.alpha / (float)r_q;
-#pragma unroll
-    for (int x = 1; x < G::NACC; ++x)
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) acc[0][rb] += acc[x][rb];
     if (rsum) {
-      row_sum_store<RB, NWV, DEEP>(a, q, acc[0], s, pw, ua, ub, u0, rfirst, rstart, rend, rtok,
+      row_sum_store<RB, NWV, DEEP>(a, q, acc, s, pw, ua, ub, u0, rfirst, rstart, rend, rtok,
                              reinterpret_cast<float*>(smem));
       continue;
     }
@@ -580,7 +724,7 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP && sizeof(T) == 2 ? 2 : 
     f32x4 h[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      h[rb] = acc[0][rb] * s;
+      h[rb] = acc[rb] * s;
 #pragma unroll
       for (int v = 0; v < 4; ++v)
         if (rank_of_row<T>(rb, 4 * g + v) >= r_q) h[rb][v] = 0.f;
@@ -589,32 +733,40 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP && sizeof(T) == 2 ? 2 : 
   }
 }
 
+// Tiles of BM rows, at most.
+long max_tiles(const ContractArgs& a, long P, int BM) { return P > 0 ? (P + BM - 1) / BM + a.keys.n_keys : 0; }
+
+template <typename T, int RB, int NRB, int NWV>
+hipError_t launch_small(const ContractArgs& a, long P, hipStream_t stream) {
+  constexpr long kGrid = 1L << 21;   // blocks per launch (a grid holds fewer than 2^32 threads)
+  const long n = max_tiles(a, P, 16 * NRB);
+  for (long t = 0; t < n; t += kGrid)
+    contract_small_kernel<T, RB, NRB, NWV><<<(int)(n - t < kGrid ? n - t : kGrid), 64 * NWV, 0, stream>>>(a, (int)t);
+  return hipGetLastError();
+}
+
+// Tiles of 16 rows (at most) up to which small batches go to contract_small:
+// above, the tiles re-read the weights too often (1000 tokens, 564 tiles: a
+// pass of the three adapters takes 105 us with it, 86 without; 400 tokens, 216
+// tiles: 67 against 71).
+constexpr long kSmallTiles = 256;
+
+// Sixteen waves, eight above 128 ranks (at sixteen the registers spill).
 template <typename T, int RB>
-hipError_t launch_contract_rb(const ContractArgs& a, long P, hipStream_t stream) {
+hipError_t launch_few_rows(const ContractArgs& a, long P, hipStream_t stream) {
+  return launch_small<T, RB, 1, RB <= 8 ? 16 : 8>(a, P, stream);
+}
+
+template <int RB>
+hipError_t launch_contract_bf16(const ContractArgs& a, long P, hipStream_t stream) {
   constexpr int NWV = 4;
-  using G = CDma<T, RB, NWV, false>;
-  const long n16 = P > 0 ? (P + 15) / 16 + a.keys.n_keys : 0;   // tiles of 16 rows, at most
-  if (n16 > 0 && n16 <= kSmallTiles && !a.row_sum) {
-    constexpr int W = RB <= 8 ? 16 : 8;   // waves (at 16 the registers of 256 ranks spill)
-    contract_small_kernel<T, RB, 1, W><<<(int)n16, 64 * W, 0, stream>>>(a);
-    return hipGetLastError();
-  }
-  // fp32 at ranks up to 64, whose matrix work fills a tile: tiles of 32 rows
-  // and four waves spread it over more blocks than the 64-row ones (OLMoE-like,
-  // 1999 tokens: 45 -> 27 us a call at rank 8, 76 -> 47 us at d 2048; group
-  // ranks up to 64 49 -> 36 us backward, level forward; 16-row tiles re-read
-  // the weights too often there, 69 us)
-  if constexpr (G::F32 && RB <= 4) {
-    const long n32 = P > 0 ? (P + 31) / 32 + a.keys.n_keys : 0;
-    if (n32 > 0) contract_small_kernel<T, RB, 2, 4><<<(int)n32, 64 * 4, 0, stream>>>(a);
-    return hipGetLastError();
-  }
-  const int TS = contract_tile(a.row_sum, a.k, G::ROWS);
-  const long tiles = P > 0 ? (P + TS - 1) / TS + a.keys.n_keys : 0;   // at most
+  using G = CDma<RB, NWV, false>;
+  if (!a.row_sum && max_tiles(a, P, 16) <= kSmallTiles) return launch_few_rows<__bf16, RB>(a, P, stream);
+  const long tiles = max_tiles(a, P, contract_tile(a.row_sum, a.k, G::ROWS));
   if constexpr (RB <= 8) {
     // one block per CU and one tile per block: see DEEP
     if (tiles > 0 && tiles <= device_cu_count()) {
-      contract_dma_kernel<T, RB, NWV, true><<<(int)tiles, G::THREADS, 0, stream>>>(a);
+      contract_dma_kernel<RB, NWV, true><<<(int)tiles, G::THREADS, 0, stream>>>(a);
       return hipGetLastError();
     }
   }
@@ -622,8 +774,52 @@ hipError_t launch_contract_rb(const ContractArgs& a, long P, hipStream_t stream)
   const long pb = P > 0 ? tiles / kXcds + a.keys.n_keys : 0;
   const long cap = (long)G::BLOCKS_PER_CU * device_cu_count() / kXcds;
   const int grid = (int)(pb < cap ? pb : cap) * kXcds;
-  if (grid > 0) contract_dma_kernel<T, RB, NWV, false><<<grid, G::THREADS, 0, stream>>>(a);
+  if (grid > 0) contract_dma_kernel<RB, NWV, false><<<grid, G::THREADS, 0, stream>>>(a);
   return hipGetLastError();
+}
+
+template <int RB>
+hipError_t launch_contract_reg(const ContractArgs& a, long P, hipStream_t stream) {
+  // tiles per bucket <= (all tiles) / kXcds + n_keys
+  const long pb = max_tiles(a, P, 16 * CReg<RB>::NRB) / kXcds + a.keys.n_keys;
+  const long cap = 6L * device_cu_count() / kXcds;
+  contract_reg_kernel<RB><<<(int)(pb < cap ? pb : cap) * kXcds, kThreads, 0, stream>>>(a);
+  return hipGetLastError();
+}
+
+// Beyond the small batches, contract_small in tiles of 32 rows (16 above 128
+// ranks) or contract_reg.  Its buckets need several tiles per key to be even
+// (64 keys of 128 pairs, rank 100, d_in 2048: 139 us with it, 67 without), and
+// there:
+//   ranks 65..128   from 1024 indices (4096 pairs through 8 keys, d_in 1024,
+//                   4096 and 14336: 41 / 43, 93 / 108, 267 / 314 us; d_in 512,
+//                   16,384 pairs: 76 / 72)
+//   ranks up to 64  where its tiles, twice as large, take half the rounds of
+//                   blocks (12,288 pairs, rank 48, d_in 2048 53 / 59, d_in 14336
+//                   242 / 311; 16,384 pairs, which take two rounds and three:
+//                   86 / 76), and from three rounds on at ranks above 32 and
+//                   4096 indices (65,536 pairs, d_in 4096 402 / 437, 14336
+//                   1239 / 1519; d_in 2048 230 / 231)
+// Above 128 ranks contract_small is ahead throughout (rank 200, d_in 2048,
+// 4096 to 32,768 pairs through 8 keys: 135 to 564 against 143 to 592).
+template <int RB>
+hipError_t launch_contract_f32(const ContractArgs& a, long P, hipStream_t stream) {
+  if constexpr (RB > 8) {
+    return launch_small<float, RB, 1, 8>(a, P, stream);
+  } else {
+    if (max_tiles(a, P, 16) <= kSmallTiles) return launch_few_rows<float, RB>(a, P, stream);
+    const long keys = a.keys.n_keys, cus = device_cu_count();
+    if constexpr (RB == 8) {
+      if (a.K >= 1024 && P >= 256 * keys) return launch_contract_reg<RB>(a, P, stream);
+      return launch_small<float, RB, 2, 8>(a, P, stream);
+    } else {
+      // rounds of blocks, with half a tile lost per key
+      const long r64 = (P / 64 + keys / 2 + cus - 1) / cus, r32 = (P / 32 + keys / 2 + cus - 1) / cus;
+      if (P >= 512 * keys && (r32 >= 2 * r64 || (RB == 4 && a.K >= 4096 && r64 >= 3)))
+        return launch_contract_reg<RB>(a, P, stream);
+      return launch_small<float, RB, 2, 4>(a, P, stream);
+    }
+  }
 }
 
 }  // namespace
@@ -644,15 +840,15 @@ hipError_t launch_contract(int dtype, const ContractArgs& a, int r_max, long P,
   if (a.row_sum && (dtype != ACE_BF16 || a.src_mode != kSrcPairList)) return hipErrorInvalidValue;
   const int rb = rank_blocks(r_max);
   if (dtype == ACE_BF16) {
-    if (rb == 2) return launch_contract_rb<__bf16, 2>(a, P, stream);
-    if (rb == 4) return launch_contract_rb<__bf16, 4>(a, P, stream);
-    if (rb == 8) return launch_contract_rb<__bf16, 8>(a, P, stream);
-    return launch_contract_rb<__bf16, 16>(a, P, stream);
+    if (rb == 2) return launch_contract_bf16<2>(a, P, stream);
+    if (rb == 4) return launch_contract_bf16<4>(a, P, stream);
+    if (rb == 8) return launch_contract_bf16<8>(a, P, stream);
+    return launch_contract_bf16<16>(a, P, stream);
   }
-  if (rb == 2) return launch_contract_rb<float, 2>(a, P, stream);
-  if (rb == 4) return launch_contract_rb<float, 4>(a, P, stream);
-  if (rb == 8) return launch_contract_rb<float, 8>(a, P, stream);
-  return launch_contract_rb<float, 16>(a, P, stream);
+  if (rb == 2) return launch_contract_f32<2>(a, P, stream);
+  if (rb == 4) return launch_contract_f32<4>(a, P, stream);
+  if (rb == 8) return launch_contract_f32<8>(a, P, stream);
+  return launch_contract_f32<16>(a, P, stream);
 }
 
 }  // namespace ace

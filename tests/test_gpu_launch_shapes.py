@@ -80,6 +80,54 @@ def test_contraction_tiles(dtype, T, E, k, groups, r_e, path):
     check_dB_rows("dB", f64(out["dB"]), dB, c.ranks, c.d_out, tol)
 
 
+# fp32 beyond the small batches: (tokens, k, d_model, group size, r) of the
+# register kernel (64-row tiles at ranks to 32 and to 64, 32-row tiles to 128)
+# and, one step away, of the 32- and 16-row tiles
+REG = [(6200, 2, 136, 2, 8), (6200, 2, 136, 4, 12), (8300, 2, 136, 4, 12), (2500, 2, 1032, 4, 25),
+       (2500, 2, 1020, 4, 25), (2500, 2, 264, 4, 40)]
+
+
+@pytest.mark.parametrize("T,k,d_model,size,r_e", REG)
+@pytest.mark.parametrize("path", ["grouped", "expertwise"])
+def test_contraction_registers_f32(T, k, d_model, size, r_e, path):
+    cfg = W.CONFIGS["olmoe_bf16"].scaled(dtype="f32", T=T, E=8, k=k, groups=("consecutive", size), r_e=r_e,
+                                         d_model=d_model, d_ffn=72)
+    say(f"f32 contraction T={T} d={d_model} r={r_e}x{size} {path}")
+    c = make_case(cfg, path, seed=4)
+    out = run_gpu(c, reuse_h=True)
+    tol = TOL["f32"]
+    check_all("y", f64(out["y"]), oracle_fwd(c), tol)
+    dx, dA, dB = oracle_bwd(c)
+    check_all("dx", f64(out["dx"]), dx, tol)
+    check_all("dA", f64(out["dA"]), dA, tol)
+    check_dB_rows("dB", f64(out["dB"]), dB, c.ranks, c.d_out, tol)
+
+
+def test_contraction_error_by_rank_f32():
+    """Every fp32 contraction sums in four chains or more, at every rank: the
+    error of a long one against 64 bits (rounding grows with the square root
+    of a chain's length) is at ranks above 64 and above 128 no larger than at
+    rank 40.  B_q = I, so that y is h; two chains would show 1.4 times."""
+    from paper_2609_06072_amd import ace
+    T, K, n = 4200, 8192, 512
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    x = torch.randn(T, K, generator=g, device="cuda")
+    A = torch.randn(256, K, generator=g, device="cuda")
+    ids = torch.zeros(T, 1, dtype=torch.int32, device="cuda")
+    rt = ace.ace_group_permute(ids, 1, None, 0, ace.ACE_ROWS_EXPERT)
+    ref = x[:n].double() @ A[:40].double().t()
+    err = {}
+    for r in (40, 100, 160, 256):
+        say(f"f32 contraction error rank {r}")
+        y = torch.zeros(T, r, device="cuda")
+        ace.ace_expertwise_lora_fwd(x, A[:r].contiguous(), torch.eye(r, device="cuda").flatten(), 1, r, float(r), rt, y)
+        err[r] = float((y[:n, :40].double() - ref).norm() / ref.norm())
+    say(str(err))
+    for r in (100, 160, 256):
+        assert err[r] <= 1.1 * err[40], err
+
+
 # rows per expert on average (T k / E): the streaming kernel's tiles of 16, 32
 # and 64 rows, the medium tiles, the large ones; d_in of one, two, three and a
 # ragged number of 64-index stages, an odd number of column tiles
