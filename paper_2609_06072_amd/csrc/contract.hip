@@ -751,10 +751,16 @@ hipError_t launch_small(const ContractArgs& a, long P, hipStream_t stream) {
 // tiles: 67 against 71).
 constexpr long kSmallTiles = 256;
 
-// Sixteen waves, eight above 128 ranks (at sixteen the registers spill).
+// Sixteen waves from 128 K-blocks (bf16 4096 indices, fp32 2048), eight below,
+// where a wave's share is a few K-blocks and the reduction over the waves
+// weighs more: bf16, rank 48, d_in 512 17.2 against 13.0 us a forward call (the
+// LDS-staged kernel 15.2), d_in 2048 17.5 and 17.3, d_in 8192 43.7 and 46.2.
+// Above 128 ranks eight (at sixteen the registers spill).
 template <typename T, int RB>
 hipError_t launch_few_rows(const ContractArgs& a, long P, hipStream_t stream) {
-  return launch_small<T, RB, 1, RB <= 8 ? 16 : 8>(a, P, stream);
+  if constexpr (RB <= 8)
+    if ((a.K + Tr<T>::KB - 1) / Tr<T>::KB >= 128) return launch_small<T, RB, 1, 16>(a, P, stream);
+  return launch_small<T, RB, 1, 8>(a, P, stream);
 }
 
 template <int RB>
