@@ -533,7 +533,6 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
   // stage buffers: NBUF source stages, then NBUF weight stages; the row sums
   // reuse the whole area for the per-pair results
   __shared__ __attribute__((aligned(16))) char smem[G::LDS];
-  const uint32_t sbase = lds_addr(smem);
   char (*Sb)[G::SBYTES] = reinterpret_cast<char (*)[G::SBYTES]>(smem);
   char (*Wb)[G::WBYTES] = reinterpret_cast<char (*)[G::WBYTES]>(smem + NBUF * G::SBYTES);
   constexpr int TAB = DEEP ? 1 : kMaxKeys + 1;   // tile tables
@@ -607,9 +606,12 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
     // weight copies this wave issues per stage (rows below r_q only)
     const int wcopies = (r_q + RPI - 1) / RPI;
     const int nw = min(G::NW, max(0, wcopies - wave * G::NW));
-    // source copies: none for rows past the segment (their results are not stored)
-    const int ns = __builtin_amdgcn_readfirstlane(
-        min(G::NS, max(0, (u_end - u0 - 16 * wave + RPI - 1) / RPI)));
+    // source copies: with DEEP none for rows past the segment (their results
+    // are not stored); otherwise those repeat the last row, since a branch per
+    // copy slows full tiles
+    const int ns = DEEP ? __builtin_amdgcn_readfirstlane(
+                              min(G::NS, max(0, (u_end - u0 - 16 * wave + RPI - 1) / RPI)))
+                        : G::NS;
 
     // source rows this lane copies (rows past the segment re-read the last
     // one) and the chunk of the row piece it copies
@@ -644,12 +646,12 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
       for (int i = 0; i < G::NS; ++i)
         if (i < ns)
           dma16(sptr[i] + min(k0 + scol[i], K - PER),
-                __builtin_amdgcn_readfirstlane(sbase + b * G::SBYTES + (16 * wave + RPI * i) * ROWB));
+                __builtin_amdgcn_readfirstlane(lds_addr(&Sb[b][(16 * wave + RPI * i) * ROWB])));
 #pragma unroll
       for (int i = 0; i < G::NW; ++i)
         if (i < nw)
           dma16(wptr[i] + min(k0 + wcol[i], K - PER),
-                __builtin_amdgcn_readfirstlane(sbase + NBUF * G::SBYTES + b * G::WBYTES + RPI * (wave * G::NW + i) * ROWB));
+                __builtin_amdgcn_readfirstlane(lds_addr(&Wb[b][RPI * (wave * G::NW + i) * ROWB])));
     };
     const int per_stage = ns + nw;   // copies per stage of this wave
 
@@ -667,31 +669,23 @@ __global__ __launch_bounds__(64 * NWV, RB == 8 && !DEEP ? 2 : 1) void contract_d
       __syncthreads();
       if (st + NBUF - 1 < nst) issue(st + NBUF - 1);
     };
-    // K-block kb of stage st; the ragged form masks the indices past the
-    // block's range
+    // K-block kb of stage st; the ragged form zeroes the fragments past the
+    // contraction (whole ones: K is a multiple of a chunk), both operands, so
+    // that an infinity there does not meet a zero
     auto kblock = [&](int st, int kb, bool ragged) {
       const int b = st % NBUF;
       const int kk = st * KC + kb * KB;
       const int chunk = kb * 4 + g;
       const int rl = 16 * wave + c16;
       F sf = *reinterpret_cast<const F*>(&Sb[b][rl * ROWB + ((chunk ^ (rl & (CPR - 1))) << 4)]);
-      if (ragged) {
-        const int nv = K - (kk + PER * g);
-#pragma unroll
-        for (int e = 0; e < PER; ++e)
-          if (e >= nv) sf[e] = (T)0.f;
-      }
+      const bool past = ragged && kk + PER * g >= K;
+      if (past) sf = Tr<T>::zero();
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         // weight rows at or past r_q were not copied: their results are zeroed below
         const int wr = rank_of_row<T>(rb, c16);
         F wf = *reinterpret_cast<const F*>(&Wb[b][wr * ROWB + ((chunk ^ w_swz<CPR>(wr)) << 4)]);
-        if (ragged) {
-          const int nv = K - (kk + PER * g);
-#pragma unroll
-          for (int e = 0; e < PER; ++e)
-            if (e >= nv) wf[e] = (T)0.f;
-        }
+        if (past) wf = Tr<T>::zero();
         acc[rb] = Tr<T>::mma(wf, sf, acc[rb]);   // D[rank][row]
       }
     };
