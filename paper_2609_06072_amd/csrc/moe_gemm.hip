@@ -225,15 +225,16 @@ __global__ __launch_bounds__(C::THREADS, 512 / C::THREADS) void moe_gemm_kernel(
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb) acc[nb][mb] = Tr<T>::mma(wf[nb], xf[mb], acc[nb][mb]);
   };
-  // The last K-block may reach past d_in: once it has landed, its x chunks
-  // past d_in (copies of the clamped last chunk) are cleared in LDS, so no
-  // fragment read needs a mask.  Called with stage st landed and published
-  // (possibly twice for the last stage: clearing again changes nothing).
+  // The last K-block may reach past d_in: once it has landed, its chunks past
+  // d_in (copies of the clamped last chunk) are cleared in LDS, so no fragment
+  // read needs a mask; those of x and of W both, since an infinity times zero
+  // is no zero.  Called with stage st landed and published (possibly twice for
+  // the last stage: clearing again changes nothing).
   auto clear_tail = [&](int st) {
     if (st != nst - 1 || d_in % KB == 0) return;
     const int valid = (d_in - st * KB) / PER;   // chunks of this K-block inside d_in
     char* S = smem + (st % NBUF) * STAGE;
-    for (int i = tid; i < BM * 4; i += NT) {
+    for (int i = tid; i < (BM + BN) * 4; i += NT) {   // x rows, then W rows (BM is a multiple of 16)
       const int row = i >> 2, pos = i & 3;
       if ((pos ^ g_swz(row)) >= valid) *reinterpret_cast<u32x4*>(S + row * kGRowBytes + pos * 16) = u32x4{0u, 0u, 0u, 0u};
     }

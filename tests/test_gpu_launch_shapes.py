@@ -161,6 +161,36 @@ def test_expert_rows_empty_and_dropped():
     check_all("y", y[keep], oracle_y(c, Wt)[keep], TOL["bf16"])
 
 
+@pytest.mark.parametrize("dtype,T", [("bf16", 9), ("bf16", 128), ("bf16", 400), ("bf16", 1100), ("f32", 20),
+                                     ("f32", 400), ("f32", 2600)])
+def test_expert_rows_infinite(dtype, T):
+    """An infinity in the last 16-byte chunk of a W row or of x, with d_in
+    that ends inside a stage: the chunks past d_in add nothing, so its products
+    stay infinite (no NaN) and the rest of y finite."""
+    from paper_2609_06072_amd import ace
+    say(f"infinite operands {dtype} T={T}")
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    E, d_in, d_out = 4, 200 if dtype == "bf16" else 204, 264
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.rand(T, d_in, generator=g, device="cuda").to(t) + 0.5
+    Wt = torch.rand(E, d_out, d_in, generator=g, device="cuda").to(t) + 0.5
+    ids = (torch.arange(T, device="cuda", dtype=torch.int32) % E)[:, None].contiguous()
+    rt = ace.ace_group_permute(ids, E, None, 0, ace.ACE_ROWS_EXPERT)
+    Wt[:, 131, d_in - 1] = float("inf")
+    x[5, d_in - 2] = float("-inf")
+    y = torch.zeros(T, d_out, dtype=t, device="cuda")
+    ace.ace_moe_lora_fwd(x, Wt, rt, y)
+    # (row 5, column 131 adds inf and -inf)
+    want = (Wt.double()[ids[:, 0].long()] * x.double()[:, None]).sum(-1)
+    inf = want.isinf()
+    assert inf.sum() == T - 1 + d_out - 1
+    assert torch.equal(y.double()[inf], want[inf])
+    fin = want.isfinite()
+    assert y[fin].isfinite().all()
+    check_all("y", f64(torch.where(fin, y, 0)), f64(torch.where(fin, want, 0)), TOL[dtype])
+
+
 @pytest.mark.parametrize("N", [8192, 9001, 16384, 16388, 20480, 24001, 28000, 32701])
 @pytest.mark.parametrize("d_in", [64, 136])
 def test_cka_probe_tiles(N, d_in):
