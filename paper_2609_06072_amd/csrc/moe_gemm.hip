@@ -136,14 +136,15 @@ __global__ __launch_bounds__(C::THREADS, 512 / C::THREADS) void moe_gemm_kernel(
   // stored.
   const bool active = u0 + 64 * wy < uend;
   const T* X = static_cast<const T*>(a.x);
-  const T* Wt = static_cast<const T*>(a.W) + (size_t)e * a.d_out * a.d_in;
+  const T* Wt = static_cast<const T*>(a.W) + ((size_t)e * a.d_out + n0) * a.d_in;
   const int d_in = a.d_in, d_out = a.d_out;
   const int nst = (d_in + KB - 1) / KB;
 
   // ---- copy assignment: lane covers row (lane >> 2) of each 16-row copy,
   // chunk position lane & 3 (global chunk (lane & 3) ^ g_swz(row)).  The
   // swizzle only sees bits 1..3 of the row, i.e. of lane >> 2, so one chunk
-  // offset serves every copy; rows are 32-bit element offsets from X or W_e.
+  // offset serves every copy; rows are 32-bit element offsets from x (fewer
+  // than 2^32 elements, see launch_moe_gemm) or from the tile's first W row.
   const int cpos = lane & 3, crl = lane >> 2;
   const int coff = PER * (cpos ^ g_swz(crl));
   uint32_t roff[COPIES];
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(C::THREADS, 512 / C::THREADS) void moe_gemm_kernel(
     const int blk = wave * COPIES + i;        // 16-row copy index over [x rows | W rows]
     const int row = 16 * blk + crl;
     roff[i] = 16 * blk < BM ? (uint32_t)s_src[row] * (uint32_t)d_in
-                            : (uint32_t)min(n0 + row - BM, d_out - 1) * (uint32_t)d_in;
+                            : (uint32_t)min(row - BM, d_out - 1 - n0) * (uint32_t)d_in;
   }
   const uint32_t sbase = lds_addr(smem);
   auto issue = [&](int st) {
@@ -378,11 +379,15 @@ __device__ inline bool locate_key(const int32_t* offsets, int n_keys, int BM, in
 
 // RAGGED: d_in is no multiple of two stages; the chunks past it are zeroed in
 // the fragments.
-template <bool RAGGED>
+// WIDE: x of 4 GiB or more (below 64 GiB): the copies' 32-bit offsets count
+// 16-byte chunks instead of bytes (300,000 rows of 8192 through 8 experts of
+// 1024 columns: 5.27 ms; the medium tiles 6.57).
+template <bool RAGGED, bool WIDE>
 __global__ __launch_bounds__(Large::THREADS, 1) void moe_gemm_large_kernel(MoeArgs a) {
   using C = Large;
   using F = bf16x8;
   constexpr int ROWB = C::ROWB, NC = C::COPIES;
+  constexpr int OU = WIDE ? 16 : 1;   // bytes per unit of the copies' offsets
   __shared__ __attribute__((aligned(16))) char smem[C::SLOTS * C::SLOT];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -448,8 +453,8 @@ __global__ __launch_bounds__(Large::THREADS, 1) void moe_gemm_large_kernel(MoeAr
 
   // ---- copies: waves 0 and 1 copy the x rows of waves (wy = 0, 1), waves 2
   // and 3 the W rows of (wx = 0, 1): of a slot the eight 8-row copies of their
-  // 64 rows, lane l the chunk at position l & 7 of row l >> 3.  Rows are byte
-  // offsets from x or from the tile's first W row; chunks past d_in repeat the
+  // 64 rows, lane l the chunk at position l & 7 of row l >> 3.  Rows are
+  // offsets (OU) from x or from the tile's first W row; chunks past d_in repeat the
   // row's last one (masked in the fragments of a ragged d_in).
   const int crl = lane >> 3, cpos = lane & 7;
   const bool xwave = wave < 2;
@@ -469,20 +474,20 @@ __global__ __launch_bounds__(Large::THREADS, 1) void moe_gemm_large_kernel(MoeAr
       } else {
         src = min(row, d_out - 1 - n0);
       }
-      roff[par][i] = (uint32_t)src * (uint32_t)(2 * d_in);
+      roff[par][i] = (uint32_t)src * (uint32_t)(2 * d_in / OU);
     }
   // chunk of the copied row: the swizzle's bit 3 alternates with i
   const int col[2] = {8 * (cpos ^ l_swz(crl)), 8 * (cpos ^ l_swz(8 + crl))};
   const uint32_t cbase = lds_addr(smem) + (xwave ? 0 : C::UNIT) + (wave & 1) * (C::UNIT / 2);
   uint32_t cslot = cbase;             // where this wave's copies of the next slot go
-  uint32_t colb[2];                   // byte column of a lane's chunk, by copy parity
+  uint32_t colb[2];                   // column (OU) of a lane's chunk, by copy parity
   auto begin_copies = [&](int v) {    // of slot P[v]
     const int st = max(0, min((v + (xwave ? 1 : 2)) >> 1, nst - 1));
 #pragma unroll
-    for (int c = 0; c < 2; ++c) colb[c] = 2 * min(st * C::KC + col[c], d_in - 8);
+    for (int c = 0; c < 2; ++c) colb[c] = 2 * min(st * C::KC + col[c], d_in - 8) / OU;
   };
   auto copy = [&](int par, int i) {
-    const char* p = base + (size_t)(roff[par][i] + colb[i & 1]);
+    const char* p = base + (size_t)(roff[par][i] + colb[i & 1]) * OU;
     dma16(p, __builtin_amdgcn_readfirstlane(cslot + i * 1024));
   };
   auto end_copies = [&]() {
@@ -796,13 +801,16 @@ hipError_t launch_moe_mid(MoeArgs a, long P, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_moe_large(MoeArgs a, long P, hipStream_t stream) {
+hipError_t launch_moe_large(MoeArgs a, long P, bool wide, hipStream_t stream) {
   a.nt = (a.d_out + Large::BN - 1) / Large::BN;
   const long max_tiles = ((P + Large::BM - 1) / Large::BM + a.E) * a.nt;
   const long grid = (max_tiles + kXcds - 1) / kXcds * kXcds;
   if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
-  if (a.d_in % (2 * Large::KC)) moe_gemm_large_kernel<true><<<(int)grid, Large::THREADS, 0, stream>>>(a);
-  else moe_gemm_large_kernel<false><<<(int)grid, Large::THREADS, 0, stream>>>(a);
+  const bool ragged = a.d_in % (2 * Large::KC) != 0;
+  if (wide && ragged) moe_gemm_large_kernel<true, true><<<(int)grid, Large::THREADS, 0, stream>>>(a);
+  else if (wide) moe_gemm_large_kernel<false, true><<<(int)grid, Large::THREADS, 0, stream>>>(a);
+  else if (ragged) moe_gemm_large_kernel<true, false><<<(int)grid, Large::THREADS, 0, stream>>>(a);
+  else moe_gemm_large_kernel<false, false><<<(int)grid, Large::THREADS, 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -833,10 +841,13 @@ hipError_t launch_moe_gemm(int dtype, const MoeArgs& a, long P, hipStream_t stre
   if (P <= kStream16 * a.E) return launch_moe_stream<__bf16, 1>(a, P, stream);
   if (P <= kStream32 * a.E) return launch_moe_stream<__bf16, 2>(a, P, stream);
   if (P <= kStream64 * a.E) return launch_moe_stream<__bf16, 4>(a, P, stream);
-  // the large tiles' x rows are 32-bit byte offsets
-  const long x_rows = a.per_pair ? P : P / a.k;
-  if (P >= kLargeRows * a.E && 2 * x_rows * a.d_in < (1L << 32)) return launch_moe_large(a, P, stream);
-  return launch_moe_mid(a, P, stream);
+  // x rows are 32-bit offsets: elements in the medium tiles, bytes or 16-byte
+  // chunks in the large ones; the streaming kernel's are pointers
+  const long x_elems = (a.per_pair ? P : P / a.k) * a.d_in;
+  const bool mid = x_elems < (1L << 32), large = 2 * x_elems < (1L << 36);
+  if (large && (P >= kLargeRows * a.E || !mid)) return launch_moe_large(a, P, 2 * x_elems >= (1L << 32), stream);
+  if (mid) return launch_moe_mid(a, P, stream);
+  return launch_moe_stream<__bf16, 4>(a, P, stream);
 }
 
 }  // namespace ace

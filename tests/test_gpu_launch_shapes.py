@@ -144,6 +144,38 @@ def test_expert_rows(dtype, T, d_model, d_ffn, r_e):
         check_all("y", f64(run_moe(c, Wt)), oracle_y(c, Wt), TOL[dtype])
 
 
+# x of 4 GiB, and of 2^32 elements, with many and with few rows per expert
+# (large tiles whose offsets count 16-byte chunks), of 64 GiB (streaming)
+@pytest.mark.parametrize("gib,E,d_in", [(4, 2, 8192), (4, 2, 8136), (8, 2, 8192), (8, 256, 131072), (8, 256, 131000),
+                                        (64, 2, 65536)])
+@pytest.mark.parametrize("mode", ["shared", "per_pair"])
+def test_expert_rows_big_x(gib, E, d_in, mode):
+    """Rows on both sides of the last one that a 32-bit offset reaches; only
+    the rows that are checked are set."""
+    from paper_2609_06072_amd import ace
+    bound = (gib << 30) // (2 * d_in)   # first row at or past gib GiB
+    T, d_out = bound + 200, 24
+    if torch.cuda.mem_get_info()[0] < (gib + 4) << 30:
+        pytest.skip("x does not fit the free memory")
+    say(f"expert rows, x of {gib} GiB, E={E} d_in={d_in} {mode}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    x = torch.empty(T, d_in, dtype=torch.bfloat16, device="cuda")
+    Wt = torch.randn(E, d_out, d_in, generator=g, device="cuda").bfloat16()
+    ids = (torch.arange(T, device="cuda", dtype=torch.int32) % E)[:, None].contiguous()
+    rt = ace.ace_group_permute(ids, E, None, 0, ace.ACE_ROWS_EXPERT)
+    rows = torch.tensor([0, 1, 199, bound // 2 - 1, bound // 2 + 1, bound - 2, bound - 1, bound, bound + 1, bound + 57,
+                         T - 1], device="cuda")
+    x[rows] = torch.randn(len(rows), d_in, generator=g, device="cuda").bfloat16()
+    y = torch.zeros(T, d_out, dtype=torch.bfloat16, device="cuda")
+    ace.ace_moe_lora_fwd(x, Wt, rt, y,
+                         input_mode=ace.ACE_INPUT_SHARED if mode == "shared" else ace.ACE_INPUT_PER_PAIR)
+    want = (Wt[ids[rows, 0].long()].double() * x[rows].double()[:, None]).sum(-1)
+    check_all("y", f64(y[rows]), f64(want), TOL["bf16"])
+    del x, y
+    torch.cuda.empty_cache()
+
+
 def test_expert_rows_empty_and_dropped():
     """Large tiles with an expert of no rows, one of a single row and dropped
     pairs: their y rows stay as they were."""
