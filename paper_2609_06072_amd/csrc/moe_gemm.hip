@@ -8,8 +8,8 @@
 // kernel.  y is written once: the adapter's read-modify-write of y is gone.
 //
 // Three kernels, chosen by the average number of rows per expert (see
-// launch_moe_gemm): streaming (few rows, any type), medium tiles and large
-// tiles (bf16).  Each cuts the rows of the expert routing (sorted by expert,
+// launch_moe_gemm): streaming (few rows), medium tiles and (bf16) large
+// tiles.  Each cuts the rows of the expert routing (sorted by expert,
 // then token) into tiles of one expert's rows; the contraction runs over d_in
 // (x rows against W_e rows, both contiguous along it) and over the adapter
 // rank (h rows against B_q rows, from registers), into the same fp32
@@ -49,7 +49,7 @@ struct GCfg {
   static_assert((BM + BN) / 16 % NW == 0, "copies must split evenly over the waves");
   static_assert(THREADS >= BM, "one thread per tile row fills the row tables");
 };
-// Medium tiles (bf16): 128 rows x 256 columns, four waves, three stages (72 KB
+// Medium tiles: 128 rows x 256 columns, four waves, three stages (72 KB
 // of LDS, two blocks per CU), so that an expert's last tile wastes little.
 using MoeMid = GCfg<2, 2, 3>;
 constexpr int kRowGroup = 8;
@@ -791,13 +791,14 @@ hipError_t launch_moe_stream(MoeArgs a, long P, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <typename T>
 hipError_t launch_moe_mid(MoeArgs a, long P, hipStream_t stream) {
   using C = MoeMid;
   a.nt = (a.d_out + C::BN - 1) / C::BN;
   const long max_tiles = ((P + C::BM - 1) / C::BM + a.E) * a.nt;
   const long grid = (max_tiles + kXcds - 1) / kXcds * kXcds;
   if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
-  if (grid > 0) moe_gemm_kernel<__bf16, C><<<(int)grid, C::THREADS, 0, stream>>>(a);
+  if (grid > 0) moe_gemm_kernel<T, C><<<(int)grid, C::THREADS, 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -825,28 +826,46 @@ hipError_t launch_moe_large(MoeArgs a, long P, bool wide, hipStream_t stream) {
 // Mixtral-like:
 //     8 rows  550 / 580 / 582, 717, 864       50 rows  1553 / 1074 / 708, 802, 886
 //   100 rows  4th 857, large 899              200 rows  medium 1296, large 947
-// fp32 has its matrix units' rate behind it in every tile, so the streaming
-// kernel stays ahead throughout (1024 x 2048, 16 experts; against the medium
-// tiles): 37 rows 187 (606), 100 rows 314 (615), 250 rows 608 (902), 1000
-// rows 2121 / 2078 with 32 / 64 rows (2286).
 constexpr long kStream16 = 8, kStream32 = 32, kStream64 = 64, kLargeRows = 192;
-constexpr long kStream32F32 = 512;
+
+// fp32, whose matrix units bound every tile.  Streaming with 16 / 32 / 64
+// rows, medium tiles, us a call: 1024 x 2048, 16 experts:
+//    24 rows    37 / 40 / 48, 138            100 rows   113 / 98 / 90, 142
+//   160 rows   155 / 131 / 128, 141          250 rows   240 / 197 / 184, 276
+//  1200 rows  1060 / 832 / 769, 682         2500 rows  2215 / 1750 / 1548, 1337
+// 4096 x 14336, 8 experts:
+//   250 rows  4654 / 2819 / 2421, 2657      2500 rows  45811 / 27690 / 22364, 18489
+// From 160 rows on the two compare by rounds: a CU takes one medium tile after
+// the other (two at once are no faster), so the call takes as long as the
+// fullest CU, at 1.2 times the rate per element of y of the streaming kernel,
+// whose small blocks even out.  Both count half a tile lost per expert.
+// (Balanced routings of about 100 rows fill the medium tiles without that loss:
+// 2048 x 1024, 64 experts 288 against 354; uneven ones at the same size 550 and
+// 390, which the host can't tell apart.)
+constexpr long kStream16F32 = 8, kStream32F32 = 160;
+
+bool mid_f32(const MoeArgs& a, long P) {
+  const long cus = device_cu_count(), BM = MoeMid::BM, BN = MoeMid::BN;
+  const long tiles = (P / BM + a.E / 2) * ((a.d_out + BN - 1) / BN);
+  return 5 * ((tiles + cus - 1) / cus * cus) * BM * BN < 6 * (P + 32 * (long)a.E) * a.d_out;
+}
 
 hipError_t launch_moe_gemm(int dtype, const MoeArgs& a, long P, hipStream_t stream) {
+  // x rows are 32-bit offsets: elements in the medium tiles, bytes or 16-byte
+  // chunks in the large ones; the streaming kernel's are pointers
+  const long x_elems = (a.per_pair ? P : P / a.k) * a.d_in;
+  const bool mid = x_elems < (1L << 32), large = 2 * x_elems < (1L << 36);
   if (dtype == ACE_F32) {
-    if (P <= kStream16 * a.E) return launch_moe_stream<float, 1>(a, P, stream);
+    if (P <= kStream16F32 * a.E) return launch_moe_stream<float, 1>(a, P, stream);
     if (P <= kStream32F32 * a.E) return launch_moe_stream<float, 2>(a, P, stream);
+    if (mid && mid_f32(a, P)) return launch_moe_mid<float>(a, P, stream);
     return launch_moe_stream<float, 4>(a, P, stream);
   }
   if (P <= kStream16 * a.E) return launch_moe_stream<__bf16, 1>(a, P, stream);
   if (P <= kStream32 * a.E) return launch_moe_stream<__bf16, 2>(a, P, stream);
   if (P <= kStream64 * a.E) return launch_moe_stream<__bf16, 4>(a, P, stream);
-  // x rows are 32-bit offsets: elements in the medium tiles, bytes or 16-byte
-  // chunks in the large ones; the streaming kernel's are pointers
-  const long x_elems = (a.per_pair ? P : P / a.k) * a.d_in;
-  const bool mid = x_elems < (1L << 32), large = 2 * x_elems < (1L << 36);
   if (large && (P >= kLargeRows * a.E || !mid)) return launch_moe_large(a, P, 2 * x_elems >= (1L << 32), stream);
-  if (mid) return launch_moe_mid(a, P, stream);
+  if (mid) return launch_moe_mid<__bf16>(a, P, stream);
   return launch_moe_stream<__bf16, 4>(a, P, stream);
 }
 

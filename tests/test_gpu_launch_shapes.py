@@ -133,7 +133,8 @@ def test_contraction_error_by_rank_f32():
 # ragged number of 64-index stages, an odd number of column tiles
 @pytest.mark.parametrize("dtype,T", [("bf16", 9), ("bf16", 32), ("bf16", 33), ("bf16", 128), ("bf16", 129),
                                      ("bf16", 256), ("bf16", 257), ("bf16", 767), ("bf16", 768),
-                                     ("bf16", 1100), ("f32", 32), ("f32", 33), ("f32", 2048), ("f32", 2049)])
+                                     ("bf16", 1100), ("f32", 32), ("f32", 33), ("f32", 640), ("f32", 641),
+                                     ("f32", 2048), ("f32", 2049)])
 @pytest.mark.parametrize("d_model,d_ffn,r_e", [(64, 128, 8), (192, 328, 24), (256, 520, 5)])
 def test_expert_rows(dtype, T, d_model, d_ffn, r_e):
     cfg = W.CONFIGS["mixtral_bf16"].scaled(dtype=dtype, T=T, k=1, E=4, d_model=d_model, d_ffn=d_ffn,
@@ -142,6 +143,19 @@ def test_expert_rows(dtype, T, d_model, d_ffn, r_e):
         say(f"expert rows {dtype} T={T} {d_model}x{d_ffn} r={r_e} {path}")
         c, Wt = case_and_weights(cfg, path, seed=12)
         check_all("y", f64(run_moe(c, Wt)), oracle_y(c, Wt), TOL[dtype])
+
+
+# 5420 to 6500 rows fill the 256 CUs with one round of 128 x 256 tiles
+@pytest.mark.parametrize("T", [5410, 5420, 6500, 6600])
+@pytest.mark.parametrize("path", ["grouped", "down_expertwise"])
+def test_expert_rows_many_f32(T, path):
+    """fp32: streaming kernel or medium tiles, with ragged columns and d_in."""
+    d_in, d_out = 204, 1276
+    dims = dict(d_model=d_in, d_ffn=d_out) if path == "grouped" else dict(d_model=d_out, d_ffn=d_in)
+    cfg = W.CONFIGS["mixtral_bf16"].scaled(dtype="f32", T=T, k=1, E=2, r_e=5, groups=("consecutive", 2), **dims)
+    say(f"expert rows f32 T={T} {path}")
+    c, Wt = case_and_weights(cfg, path, seed=14)
+    check_all("y", f64(run_moe(c, Wt)), oracle_y(c, Wt), TOL["f32"])
 
 
 # x of 4 GiB, and of 2^32 elements, with many and with few rows per expert
