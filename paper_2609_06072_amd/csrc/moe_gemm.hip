@@ -551,16 +551,16 @@ __global__ __launch_bounds__(Large::THREADS, 1) void moe_gemm_large_kernel(MoeAr
     const char* xs1 = smem + rslot + (xl ^ 64);
     const char* ws1 = smem + rslot + (wl ^ 64);
     begin_copies(v + 4);
-    if (RAGGED && MMA && PAR == 0) {
-      const int c = (v >> 1) * C::KC + 8 * g;
+    const int c = (v >> 1) * C::KC + 8 * g;
+    const bool past = RAGGED && MMA && (v >> 1) * C::KC + C::KC > d_in;   // wave-uniform
+    if (PAR == 0 && past) {
 #pragma unroll
       for (int nb = 0; nb < 8; ++nb) {
         if (c >= d_in) wc[nb] = Tr<__bf16>::zero();
         if (c + 32 >= d_in) wc[nb + 8] = Tr<__bf16>::zero();
       }
     }
-    if (RAGGED && MMA) {
-      const int c = (v >> 1) * C::KC + 8 * g;
+    if (past) {
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb) {
         if (c >= d_in) x0[mb] = Tr<__bf16>::zero();
