@@ -378,7 +378,10 @@ __device__ inline bool locate_key(const int32_t* offsets, int n_keys, int BM, in
 }
 
 // RAGGED: d_in is no multiple of two stages; the chunks past it are zeroed in
-// the fragments.
+// the fragments, behind a branch: done in every half-step, on the one wave of
+// a SIMD that has nothing to hide it behind, it cost a sixth (1000 x 2056, 16
+// experts, 1000 and 2000 rows each: 141 -> 120 and 228 -> 196 us).  (A second
+// loop for the last stages made the compiler spill accumulators.)
 // WIDE: x of 4 GiB or more (below 64 GiB): the copies' 32-bit offsets count
 // 16-byte chunks instead of bytes (300,000 rows of 8192 through 8 experts of
 // 1024 columns: 5.27 ms; the medium tiles 6.57).
@@ -817,16 +820,33 @@ hipError_t launch_moe_large(MoeArgs a, long P, bool wide, hipStream_t stream) {
 
 }  // namespace
 
-// Which kernel, by the average number of rows per expert, P / E.  Passes of
-// the three projections in us (streaming with 16 / 32 / 64 rows, medium,
-// large), OLMoE-like shapes:
-//     6 rows  202 / 199 / 200, 231, 266       25 rows  264 / 233 / 245, 306, 288
-//    62 rows  435 / 362 / 302, 323, 430      125 rows  684 / 534 / 455, 341, 425
-//   250 rows  medium 477, large 457          512 rows  medium 680, large 643
-// Mixtral-like:
-//     8 rows  550 / 580 / 582, 717, 864       50 rows  1553 / 1074 / 708, 802, 886
-//   100 rows  4th 857, large 899              200 rows  medium 1296, large 947
-constexpr long kStream16 = 8, kStream32 = 32, kStream64 = 64, kLargeRows = 192;
+// bf16: which kernel, by the average number of rows per expert, P / E.  A
+// second tile of an expert costs its weights a second time, so an average
+// close to a tile's rows already loses (random routings, weights out of every
+// cache, us a call: streaming with 16 / 32 / 64 rows, medium, large; even
+// routing, then one with popularity ~ 1 / rank^0.8):
+//   2048 x 1024, 64 experts (256 medium tiles of one per expert)
+//      8 rows   54 /  60 /  56,  69,  76      57 /  58 /  57,  71,  76
+//     32 rows   86 /  71 /  60,  70,  77      83 /  67 /  67,  95,  84
+//     48 rows  111 /  92 /  70,  70,  78     105 /  87 /  75,  93, 121
+//     64 rows  134 / 104 /  84,  71,  79     129 /  99 /  81,  96, 119
+//    192 rows  277 / 204 / 173,  95,  83     289 / 209 / 177, 101, 118
+//    400 rows  524 / 369 / 310, 166, 124     532 / 373 / 311, 163, 124
+//   1024 x 2048, 64 experts (512)
+//     24 rows   69 /  53 /  60,  56,  75      68 /  60 /  64,  73,  76
+//     32 rows   82 /  67 /  62,  57,  76      81 /  66 /  68,  75,  78
+//   4096 x 14336, 8 experts (448)
+//     16 rows  203 / 182 / 184, 177, 210     199 / 180 / 182, 179, 210
+//     32 rows  346 / 237 / 195, 183, 208     325 / 212 / 193, 191, 208
+//     64 rows  633 / 389 / 282, 195, 210     632 / 375 / 253, 207, 210
+//   14336 x 4096, 8 experts (128)
+//     24 rows  270 / 141 / 145, 287, 309     252 / 192 / 145, 293, 307
+//     64 rows  558 / 373 / 329, 305, 303     556 / 346 / 275, 316, 307
+// So 32-row tiles end at 20 rows; 64-row tiles at 48, or at 64 where the
+// medium tiles leave CUs idle; and where there are medium tiles for all CUs
+// one and a half times, they take over from the 32-row tiles at 24.
+constexpr long kStream16 = 8, kStream32 = 20, kStream64 = 48, kStream64Few = 64, kMidMany = 24;
+constexpr long kLargeRows = 192;
 
 // fp32, whose matrix units bound every tile.  Streaming with 16 / 32 / 64
 // rows, medium tiles, us a call: 1024 x 2048, 16 experts:
@@ -861,9 +881,12 @@ hipError_t launch_moe_gemm(int dtype, const MoeArgs& a, long P, hipStream_t stre
     if (mid && mid_f32(a, P)) return launch_moe_mid<float>(a, P, stream);
     return launch_moe_stream<float, 4>(a, P, stream);
   }
+  const long cus = device_cu_count(), tiles = (long)a.E * ((a.d_out + MoeMid::BN - 1) / MoeMid::BN);
+  const bool many = 2 * tiles >= 3 * cus;   // medium tiles, one per expert
   if (P <= kStream16 * a.E) return launch_moe_stream<__bf16, 1>(a, P, stream);
-  if (P <= kStream32 * a.E) return launch_moe_stream<__bf16, 2>(a, P, stream);
-  if (P <= kStream64 * a.E) return launch_moe_stream<__bf16, 4>(a, P, stream);
+  if (P <= (many ? kMidMany : kStream32) * a.E) return launch_moe_stream<__bf16, 2>(a, P, stream);
+  if (!many && P <= (4 * tiles < 3 * cus ? kStream64Few : kStream64) * a.E)
+    return launch_moe_stream<__bf16, 4>(a, P, stream);
   if (large && (P >= kLargeRows * a.E || !mid)) return launch_moe_large(a, P, 2 * x_elems >= (1L << 32), stream);
   if (mid) return launch_moe_mid<__bf16>(a, P, stream);
   return launch_moe_stream<__bf16, 4>(a, P, stream);

@@ -131,8 +131,8 @@ def test_contraction_error_by_rank_f32():
 # rows per expert on average (T k / E): the streaming kernel's tiles of 16, 32
 # and 64 rows, the medium tiles, the large ones; d_in of one, two, three and a
 # ragged number of 64-index stages, an odd number of column tiles
-@pytest.mark.parametrize("dtype,T", [("bf16", 9), ("bf16", 32), ("bf16", 33), ("bf16", 128), ("bf16", 129),
-                                     ("bf16", 256), ("bf16", 257), ("bf16", 767), ("bf16", 768),
+@pytest.mark.parametrize("dtype,T", [("bf16", 9), ("bf16", 32), ("bf16", 33), ("bf16", 80), ("bf16", 81),
+                                     ("bf16", 128), ("bf16", 129), ("bf16", 256), ("bf16", 257), ("bf16", 767), ("bf16", 768),
                                      ("bf16", 1100), ("f32", 32), ("f32", 33), ("f32", 640), ("f32", 641),
                                      ("f32", 2048), ("f32", 2049)])
 @pytest.mark.parametrize("d_model,d_ffn,r_e", [(64, 128, 8), (192, 328, 24), (256, 520, 5)])
@@ -143,6 +143,16 @@ def test_expert_rows(dtype, T, d_model, d_ffn, r_e):
         say(f"expert rows {dtype} T={T} {d_model}x{d_ffn} r={r_e} {path}")
         c, Wt = case_and_weights(cfg, path, seed=12)
         check_all("y", f64(run_moe(c, Wt)), oracle_y(c, Wt), TOL[dtype])
+
+
+# where the medium tiles leave few CUs idle (224 of one per expert) they take
+# over from 48 rows per expert, where they fill them (384) from 24
+@pytest.mark.parametrize("E,T", [(56, 20), (56, 21), (56, 48), (56, 49), (96, 20), (96, 24), (96, 25)])
+def test_expert_rows_many_experts(E, T):
+    cfg = W.CONFIGS["mixtral_bf16"].scaled(T=T * E, k=1, E=E, d_model=72, d_ffn=1000, r_e=4, groups=("consecutive", 4))
+    say(f"expert rows of {E} experts, {T} each")
+    c, Wt = case_and_weights(cfg, "grouped", seed=15)
+    check_all("y", f64(run_moe(c, Wt)), oracle_y(c, Wt), TOL["bf16"])
 
 
 # 5420 to 6500 rows fill the 256 CUs with one round of 128 x 256 tiles
