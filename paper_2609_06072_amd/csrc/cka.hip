@@ -115,7 +115,7 @@ __device__ inline void upper_pair(int p, int n, int* a, int* b) {
 
 // ---------------------------------------------------------------- project
 
-// A block takes PN probe rows x 256 adapter rows (eight waves, so that X is
+// fp32 inputs: a block takes PN probe rows x 256 adapter rows (eight waves, so that X is
 // staged once per 256 adapter rows); wave (wn, wc) owns PN / 2 x 64.
 // Stages of two K-blocks (128 bytes of every row) of both operands are
 // copied global -> LDS with global_load_lds_dwordx4, NBUF stages in LDS (no
@@ -130,9 +130,10 @@ __device__ inline int cka_sw(int row) { return (row >> 1) & 7; }
 // The same for 64-byte rows (four chunks; the Gram's stages): (row >> 2) & 3.
 __device__ inline int cka_sw4(int row) { return (row >> 2) & 3; }
 
-template <typename T, int PN, int NBUF>
 __global__ __launch_bounds__(kPThreads) void cka_project_kernel(CkaArgs a) {
-  using F = typename Tr<T>::frag;
+  using T = float;
+  using F = Tr<T>::frag;
+  constexpr int PN = kPN, NBUF = kPBuf;
   constexpr int PER = Tr<T>::PER, KB = Tr<T>::KB;   // KB * sizeof(T) = 64 bytes
   constexpr int KS = 2 * KB;                        // contraction indices per stage (128 bytes)
   constexpr int RB = 128;                           // bytes of a row per stage
@@ -961,7 +962,7 @@ hipError_t launch_cka_t(const CkaProblem& p, void* ws, hipStream_t stream) {
       launch_project(a, stream);
     } else {
       const dim3 grid((p.N + kPN - 1) / kPN, (R + kPC - 1) / kPC);
-      cka_project_kernel<float, kPN, kPBuf><<<grid, kPThreads, 0, stream>>>(a);
+      cka_project_kernel<<<grid, kPThreads, 0, stream>>>(a);
     }
   }
   if (p.dtype == ACE_BF16)
