@@ -283,9 +283,11 @@ __device__ inline int upper_index(const int* arr, int n, int x) {
 
 // D += A B with D held in accumulation registers: left to itself the compiler
 // copies accumulators (within or between the register files) on the edges of
-// loops that hold many of them.  The compiler's hazard tables don't see the instruction: s_nop covers
-// operands written by a vector instruction right before it, and mfma_done()
-// stands between the last one and the first read of an accumulator.
+// loops that hold many of them.  The compiler's hazard tables don't see the
+// instruction: s_nop covers operands written by a vector instruction right
+// before it, and mfma_done() stands between the last one and the first read of
+// an accumulator.  A copy or a spill that the compiler itself places between
+// them would read too early; the test of these waits looks for any.
 __device__ inline void mfma_acc(f32x4& d, bf16x8 a, bf16x8 b) {
   asm("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
 }

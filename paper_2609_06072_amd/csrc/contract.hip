@@ -417,7 +417,7 @@ __global__ __launch_bounds__(kThreads) void contract_reg_kernel(ContractArgs a) 
 // DEEP: with no more tiles than CUs (decode batches) a block is alone on its
 // CU and every stage would cost a round trip to memory: the stages fill the
 // LDS instead of sharing it with other blocks, a block takes one tile, found
-// without barriers.  OLMoE-like, 1000 tokens (188 tiles at most): a pass of
+// without barriers.  OLMoE-like, 1000 tokens (189 tiles at most): a pass of
 // the three adapters 96 -> 86 us.
 template <int RB, int NWV, bool DEEP>
 struct CDma {

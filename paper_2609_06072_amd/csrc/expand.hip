@@ -300,7 +300,11 @@ hipError_t launch_expand_rb(ExpandArgs a, long P, hipStream_t stream) {
   // one batch of loads (a second batch costs a round trip to the memory).
   // fp32, whose pairs have twice the pieces, covers 64 pairs with eight of one
   // chunk and takes 48 rows throughout: against 64 rows and six pieces the
-  // OLMoE-like step of 1999 tokens 916 -> 889 us, 256 tokens 66.6 -> 56.3 us
+  // OLMoE-like step of 1999 tokens 916 -> 889 us, 256 tokens 66.6 -> 56.3 us.
+  // Wide outputs keep one chunk too: rank 16, d_in 512, 14,336 columns, a
+  // forward call of 500, 2000 and 8000 tokens through 16 keys 41, 120 and 424
+  // us, 49, 126 and 423 with two chunks of 64-row tiles (and the register
+  // kernel's contraction)
   const int bm = F32 || (a.multi_slot && nc == 2) ? kBM48 : kBM;
   // tiles are bounded by P / bm plus one ragged tile per key; U itself stays
   // on the device
