@@ -56,6 +56,7 @@ struct ContractArgs {
   const int32_t* offsets;
   const int32_t* row_token;
   const uint32_t* row_slots;
+  int32_t multi_slot;         // rows may serve several slots: fewer of them than pairs
   void* out_row;              // [U][rpad] or null
   int32_t rpad;
   void* out_t;                // [R][ldh] (column u - offsets[q]) or null

@@ -795,11 +795,17 @@ hipError_t launch_contract_reg(const ContractArgs& a, long P, hipStream_t stream
 //                   4096 and 14336: 41 / 43, 93 / 108, 267 / 314 us; d_in 512,
 //                   16,384 pairs: 76 / 72)
 //   ranks up to 64  where its tiles, twice as large, take half the rounds of
-//                   blocks (12,288 pairs, rank 48, d_in 2048 53 / 59, d_in 14336
-//                   242 / 311; 16,384 pairs, which take two rounds and three:
-//                   86 / 76), and from three rounds on at ranks above 32 and
-//                   4096 indices (65,536 pairs, d_in 4096 402 / 437, 14336
-//                   1239 / 1519; d_in 2048 230 / 231)
+//                   blocks: contract_reg / contract_small at d_in 2048 and 8192,
+//                   8 keys, rank 32 12,000 rows 35 / 44 and 97 / 127; 16,000, two
+//                   rounds of both, 66 / 46 and 223 / 129; 32,000, two and four,
+//                   74 / 76 and 240 / 251; rank 64 53 / 66 and 152 / 197, 95 / 69
+//                   and 291 / 202, 107 / 127 and 319 / 424; and from three rounds
+//                   on at ranks above 32 and 4096 indices (65,536 pairs, d_in 4096
+//                   402 / 437, 14336 1239 / 1519; d_in 2048 230 / 231).
+//                   contract_reg's blocks take fixed XCDs, so it needs some tiles
+//                   less than CUs for a single round (250 full ones and 4 ragged
+//                   took two); where rows serve several slots there are fewer than
+//                   pairs (15 keys of four experts, top 4: 7%)
 // Above 128 ranks contract_small is ahead throughout (rank 200, d_in 2048,
 // 4096 to 32,768 pairs through 8 keys: 135 to 564 against 143 to 592).
 template <int RB>
@@ -813,8 +819,8 @@ hipError_t launch_contract_f32(const ContractArgs& a, long P, hipStream_t stream
       if (a.K >= 1024 && P >= 256 * keys) return launch_contract_reg<RB>(a, P, stream);
       return launch_small<float, RB, 2, 8>(a, P, stream);
     } else {
-      // rounds of blocks, with half a tile lost per key
-      const long r64 = (P / 64 + keys / 2 + cus - 1) / cus, r32 = (P / 32 + keys / 2 + cus - 1) / cus;
+      const long rows = a.multi_slot ? P - P / 16 : P;
+      const long r64 = (rows / 64 + keys + 4 + cus - 1) / cus, r32 = (rows / 32 + cus - 1) / cus;
       if (P >= 512 * keys && (r32 >= 2 * r64 || (RB == 4 && a.K >= 4096 && r64 >= 3)))
         return launch_contract_reg<RB>(a, P, stream);
       return launch_small<float, RB, 2, 4>(a, P, stream);

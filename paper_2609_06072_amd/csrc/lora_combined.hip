@@ -269,6 +269,7 @@ hipError_t launch_bwd_combined(const Problem& p, const void* dy, void* dx, float
   c.offsets = p.rt->offsets;
   c.row_token = p.rt->row_token;
   c.row_slots = p.rt->row_slots;
+  c.multi_slot = p.rt->mode == ACE_ROWS_GROUP_DEDUP;
   c.out_row = base + L.dHrow;
   c.rpad = rpad;
   c.out_t = base + L.dHw;

@@ -26,6 +26,7 @@ hipError_t launch_shrink(const Problem& p, void* h, hipStream_t stream) {
   c.offsets = p.rt->offsets;
   c.row_token = p.rt->row_token;
   c.row_slots = p.rt->row_slots;
+  c.multi_slot = p.rt->mode == ACE_ROWS_GROUP_DEDUP;
   c.out_row = h;
   c.rpad = rank_pad(p.dtype, p.r_max);
   c.keys = p.keys;
