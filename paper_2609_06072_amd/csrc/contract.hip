@@ -15,6 +15,8 @@
 //   row-major  [U][rpad]      operand of the expand kernel (zero beyond r_q)
 //   per key    [R][ldh]       column u - offsets[q]: operand of the column pass
 //   dense      [T*kslots][R]  per-token rows: operand of the dense dx GEMM
+#include <type_traits>
+
 #include "ace_device.hpp"
 #include "ace_internal.hpp"
 
@@ -108,6 +110,11 @@ __device__ inline void contract_store(const ContractArgs& a, int q, int lo, int 
 // d_in 512 and 1024: 11.5 -> 8.8 and 15.2 -> 7.8 us.
 // fp32, whose matrix work fills a tile, also takes larger batches this way, in
 // tiles of 32 rows up to 128 ranks (launch_contract_f32).
+// Tiles per grid row (a dimension holds fewer than 2^32 threads; a first tile
+// passed as an argument is one more scalar load ahead of the tile search: 0.3
+// of 8 us).
+constexpr int kSmallGrid = 1 << 21;
+
 // NRB row blocks of 16 per tile, NWV waves
 template <int RB, int NRB_, int NWV_>
 struct CSmall {
@@ -117,7 +124,7 @@ struct CSmall {
 };
 
 template <typename T, int RB, int NRB, int NWV>
-__global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a, int tile0) {
+__global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a) {
   using F = typename Tr<T>::frag;
   using G = CSmall<RB, NRB, NWV>;
   constexpr int PER = Tr<T>::PER, KB = Tr<T>::KB, SU = G::SU;
@@ -126,7 +133,7 @@ __global__ __launch_bounds__(64 * NWV) void contract_small_kernel(ContractArgs a
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, g = lane >> 4;
   int q, u0, u_end, lo;
-  if (!locate_tile(a.offsets, n_keys, 16 * NRB, tile0 + blockIdx.x, &q, &u0, &u_end,
+  if (!locate_tile(a.offsets, n_keys, 16 * NRB, blockIdx.y * kSmallGrid + blockIdx.x, &q, &u0, &u_end,
                    a.src_mode == kSrcPairList ? a.ppos : nullptr, &lo))
     return;
   q = __builtin_amdgcn_readfirstlane(q);
@@ -732,10 +739,9 @@ long max_tiles(const ContractArgs& a, long P, int BM) { return P > 0 ? (P + BM -
 
 template <typename T, int RB, int NRB, int NWV>
 hipError_t launch_small(const ContractArgs& a, long P, hipStream_t stream) {
-  constexpr long kGrid = 1L << 21;   // blocks per launch (a grid holds fewer than 2^32 threads)
   const long n = max_tiles(a, P, 16 * NRB);
-  for (long t = 0; t < n; t += kGrid)
-    contract_small_kernel<T, RB, NRB, NWV><<<(int)(n - t < kGrid ? n - t : kGrid), 64 * NWV, 0, stream>>>(a, (int)t);
+  const dim3 grid((unsigned)(n < kSmallGrid ? n : kSmallGrid), (unsigned)((n + kSmallGrid - 1) / kSmallGrid));
+  if (n > 0) contract_small_kernel<T, RB, NRB, NWV><<<grid, 64 * NWV, 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -745,15 +751,18 @@ hipError_t launch_small(const ContractArgs& a, long P, hipStream_t stream) {
 // tiles: 67 against 71).
 constexpr long kSmallTiles = 256;
 
-// Sixteen waves from 128 K-blocks (bf16 4096 indices, fp32 2048), eight below,
-// where a wave's share is a few K-blocks and the reduction over the waves
-// weighs more: bf16, rank 48, d_in 512 17.2 against 13.0 us a forward call (the
-// LDS-staged kernel 15.2), d_in 2048 17.5 and 17.3, d_in 8192 43.7 and 46.2.
-// Above 128 ranks eight (at sixteen the registers spill).
+// bf16: sixteen waves from 128 K-blocks (4096 indices), eight below, where a
+// wave's share is a few K-blocks and the reduction over the waves weighs more:
+// rank 48, d_in 512 17.2 against 13.0 us a forward call (the LDS-staged kernel
+// 15.2), d_in 2048 17.5 and 17.3, d_in 8192 43.7 and 46.2.  fp32 sums in
+// sixteen chains throughout: eight are 1.4 us of 56 a tiny training step
+// faster, and off by 2.9e-7 from 64 bits where sixteen are by 2.5e-7.  Above
+// 128 ranks eight (at sixteen the registers spill).
 template <typename T, int RB>
 hipError_t launch_few_rows(const ContractArgs& a, long P, hipStream_t stream) {
   if constexpr (RB <= 8)
-    if ((a.K + Tr<T>::KB - 1) / Tr<T>::KB >= 128) return launch_small<T, RB, 1, 16>(a, P, stream);
+    if (std::is_same<T, float>::value || (a.K + Tr<T>::KB - 1) / Tr<T>::KB >= 128)
+      return launch_small<T, RB, 1, 16>(a, P, stream);
   return launch_small<T, RB, 1, 8>(a, P, stream);
 }
 

@@ -128,6 +128,28 @@ def test_contraction_error_by_rank_f32():
         assert err[r] <= 1.1 * err[40], err
 
 
+def test_contraction_second_grid_row_f32():
+    """More than 2^21 tiles of 16 rows: the rows of the grid's second row."""
+    from paper_2609_06072_amd import ace
+    T, r, d = (1 << 25) + 1000, 130, 4
+    if torch.cuda.mem_get_info()[0] < 40 << 30:
+        pytest.skip("h does not fit the free memory")
+    say("f32 contraction of 2^25 rows")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    x = torch.randn(T, d, generator=g, device="cuda")
+    A, B = torch.randn(r, d, generator=g, device="cuda"), torch.randn(d, r, generator=g, device="cuda")
+    ids = torch.zeros(T, 1, dtype=torch.int32, device="cuda")
+    rt = ace.ace_group_permute(ids, 1, None, 0, ace.ACE_ROWS_EXPERT)
+    y = torch.zeros(T, d, device="cuda")
+    ace.ace_expertwise_lora_fwd(x, A, B.flatten(), 1, r, 2.0 * r, rt, y)
+    for rows in (slice(0, 500), slice((1 << 25) - 500, T)):
+        want = 2.0 * (x[rows].double() @ A.double().t()) @ B.double().t()
+        check_all("y", f64(y[rows]), f64(want), TOL["f32"])
+    del x, y, rt
+    torch.cuda.empty_cache()
+
+
 # rows per expert on average (T k / E): the streaming kernel's tiles of 16, 32
 # and 64 rows, the medium tiles, the large ones; d_in of one, two, three and a
 # ragged number of 64-index stages, an odd number of column tiles
