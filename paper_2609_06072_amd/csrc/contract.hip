@@ -806,15 +806,18 @@ hipError_t launch_contract_reg(const ContractArgs& a, long P, hipStream_t stream
 //   ranks up to 64  where its tiles, twice as large, take half the rounds of
 //                   blocks: contract_reg / contract_small at d_in 2048 and 8192,
 //                   8 keys, rank 32 12,000 rows 35 / 44 and 97 / 127; 16,000, two
-//                   rounds of both, 66 / 46 and 223 / 129; 32,000, two and four,
-//                   74 / 76 and 240 / 251; rank 64 53 / 66 and 152 / 197, 95 / 69
-//                   and 291 / 202, 107 / 127 and 319 / 424; and from three rounds
-//                   on at ranks above 32 and 4096 indices (65,536 pairs, d_in 4096
-//                   402 / 437, 14336 1239 / 1519; d_in 2048 230 / 231).
-//                   contract_reg's blocks take fixed XCDs, so it needs some tiles
-//                   less than CUs for a single round (250 full ones and 4 ragged
-//                   took two); where rows serve several slots there are fewer than
-//                   pairs (15 keys of four experts, top 4: 7%)
+//                   rounds of both, 66 / 46 and 223 / 129; rank 64 53 / 66 and
+//                   152 / 197, 95 / 69 and 291 / 202; 32,000, two and four, 107 /
+//                   127 and 319 / 424 (rank 32 74 / 76 and 240 / 251: one round
+//                   only up to there); and from three rounds on at ranks above
+//                   32 and 4096 indices (65,536 pairs, d_in 4096 402 / 437, 14336
+//                   1239 / 1519; d_in 2048 230 / 231)
+// contract_reg's tiles are dealt to the XCDs key by key, so its rounds are
+// counted with half a tile per key and XCD more than the rows fill (15 keys of
+// 2133 rows, 508 tiles, took three rounds).  Rows that serve several slots are
+// fewer than pairs, at most one per token and key; how many fewer the routing
+// decides (7% with 15 even keys of four experts, top 4), so either kernel's
+// rounds are counted on the safe side.
 // Above 128 ranks contract_small is ahead throughout (rank 200, d_in 2048,
 // 4096 to 32,768 pairs through 8 keys: 135 to 564 against 143 to 592).
 template <int RB>
@@ -828,9 +831,11 @@ hipError_t launch_contract_f32(const ContractArgs& a, long P, hipStream_t stream
       if (a.K >= 1024 && P >= 256 * keys) return launch_contract_reg<RB>(a, P, stream);
       return launch_small<float, RB, 2, 8>(a, P, stream);
     } else {
-      const long rows = a.multi_slot ? P - P / 16 : P;
-      const long r64 = (rows / 64 + keys + 4 + cus - 1) / cus, r32 = (rows / 32 + cus - 1) / cus;
-      if (P >= 512 * keys && (r32 >= 2 * r64 || (RB == 4 && a.K >= 4096 && r64 >= 3)))
+      const long most = a.multi_slot && P / a.k * keys < P ? P / a.k * keys : P;
+      const long r64 = (most / 64 + 4 * keys + cus - 1) / cus;
+      const long r32 = ((a.multi_slot ? most * 3 / 4 : most) / 32 + cus - 1) / cus;
+      if (P >= 512 * keys && ((r32 >= 2 * r64 && (RB == 4 || r64 == 1)) ||
+                              (RB == 4 && a.K >= 4096 && r64 >= 3)))
         return launch_contract_reg<RB>(a, P, stream);
       return launch_small<float, RB, 2, 4>(a, P, stream);
     }
