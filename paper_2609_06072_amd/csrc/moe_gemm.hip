@@ -842,10 +842,14 @@ hipError_t launch_moe_large(MoeArgs a, long P, bool wide, hipStream_t stream) {
 //   14336 x 4096, 8 experts (128)
 //     24 rows  270 / 141 / 145, 287, 309     252 / 192 / 145, 293, 307
 //     64 rows  558 / 373 / 329, 305, 303     556 / 346 / 275, 316, 307
-// So 32-row tiles end at 20 rows; 64-row tiles at 48, or at 64 where the
-// medium tiles leave CUs idle; and where there are medium tiles for all CUs
-// one and a half times, they take over from the 32-row tiles at 24.
-constexpr long kStream16 = 8, kStream32 = 20, kStream64 = 48, kStream64Few = 64, kMidMany = 24;
+//   1000 x 2056, 16 experts (144)
+//     24 rows   31 /  22 /  24,  34,  36      35 /  24 /  28,  37,  36
+//     64 rows   71 /  46 /  34,  38,  37      71 /  46 /  33,  42,  42
+// So 32-row tiles end at 20 rows, 64-row tiles at 48; where the medium tiles
+// leave CUs idle, at 28 (contractions below 4096) and 64; and where there are
+// medium tiles for all CUs one and a half times, they take over from the
+// 32-row tiles at 24.
+constexpr long kStream16 = 8, kStream32 = 20, kStream64 = 48, kStream32Few = 28, kStream64Few = 64, kMidMany = 24;
 constexpr long kLargeRows = 192;
 
 // fp32, whose matrix units bound every tile.  Streaming with 16 / 32 / 64
@@ -882,11 +886,11 @@ hipError_t launch_moe_gemm(int dtype, const MoeArgs& a, long P, hipStream_t stre
     return launch_moe_stream<float, 4>(a, P, stream);
   }
   const long cus = device_cu_count(), tiles = (long)a.E * ((a.d_out + MoeMid::BN - 1) / MoeMid::BN);
-  const bool many = 2 * tiles >= 3 * cus;   // medium tiles, one per expert
+  const bool many = 2 * tiles >= 3 * cus, few = 4 * tiles < 3 * cus;   // medium tiles, one per expert
+  const long stream32 = many ? kMidMany : few && a.d_in < 4096 ? kStream32Few : kStream32;
   if (P <= kStream16 * a.E) return launch_moe_stream<__bf16, 1>(a, P, stream);
-  if (P <= (many ? kMidMany : kStream32) * a.E) return launch_moe_stream<__bf16, 2>(a, P, stream);
-  if (!many && P <= (4 * tiles < 3 * cus ? kStream64Few : kStream64) * a.E)
-    return launch_moe_stream<__bf16, 4>(a, P, stream);
+  if (P <= stream32 * a.E) return launch_moe_stream<__bf16, 2>(a, P, stream);
+  if (!many && P <= (few ? kStream64Few : kStream64) * a.E) return launch_moe_stream<__bf16, 4>(a, P, stream);
   if (large && (P >= kLargeRows * a.E || !mid)) return launch_moe_large(a, P, 2 * x_elems >= (1L << 32), stream);
   if (mid) return launch_moe_mid<__bf16>(a, P, stream);
   return launch_moe_stream<__bf16, 4>(a, P, stream);

@@ -154,7 +154,7 @@ def test_contraction_second_grid_row_f32():
 # and 64 rows, the medium tiles, the large ones; d_in of one, two, three and a
 # ragged number of 64-index stages, an odd number of column tiles
 @pytest.mark.parametrize("dtype,T", [("bf16", 9), ("bf16", 32), ("bf16", 33), ("bf16", 80), ("bf16", 81),
-                                     ("bf16", 128), ("bf16", 129), ("bf16", 256), ("bf16", 257), ("bf16", 767), ("bf16", 768),
+                                     ("bf16", 112), ("bf16", 113), ("bf16", 128), ("bf16", 129), ("bf16", 256), ("bf16", 257), ("bf16", 767), ("bf16", 768),
                                      ("bf16", 1100), ("f32", 32), ("f32", 33), ("f32", 640), ("f32", 641),
                                      ("f32", 2048), ("f32", 2049)])
 @pytest.mark.parametrize("d_model,d_ffn,r_e", [(64, 128, 8), (192, 328, 24), (256, 520, 5)])
